@@ -16,14 +16,10 @@
 #include <utility>
 
 #include "krylov.h"
+#include "wave.h"
 
 namespace llg {
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
@@ -56,12 +52,14 @@ template <int MAXV, bool MAX = false>
 __device__ __forceinline__ void block_store(double (&acc)[MAXV], int nv, double* __restrict__ partial) {
   __shared__ double sm[kRedThreads / 64][MAXV];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if constexpr (MAX) {
 #pragma unroll
-  for (int i = 0; i < MAXV; ++i) {
-    if (i < nv) {
-      const double s = MAX ? wave_max(acc[i]) : wave_sum(acc[i]);
+    for (int i = 0; i < MAXV; ++i) {
+      const double s = wave_max(acc[i]);
       if (lane == 0) sm[wv][i] = s;
     }
+  } else {
+    wave_sums_store<MAXV>(acc, sm[wv]);
   }
   __syncthreads();
   if (threadIdx.x < nv) {
@@ -238,12 +236,7 @@ template <int NV>
 __device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double* __restrict__ partial,
                                                  double* __restrict__ mirror = nullptr) {
   __shared__ double sm[kDcgsThreads / 64][NV];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const double y = wave_sum(acc[i]);
-    if (lane == 0) sm[wv][i] = y;
-  }
+  wave_sums_store<NV>(acc, sm[threadIdx.x >> 6]);
   __syncthreads();
   if (threadIdx.x < NV) {
     double t = sm[0][threadIdx.x];

@@ -11,14 +11,10 @@
 #include <cmath>
 
 #include "krylov.h"
+#include "wave.h"
 
 namespace llg {
 
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 __device__ __forceinline__ double wmax(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
@@ -30,13 +26,14 @@ template <int NV, int OP>
 __device__ __forceinline__ void bstore(double (&acc)[NV], double* __restrict__ partial) {
   __shared__ double sm[kRedThreads / 64][NV];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if constexpr (OP == 0) {
+    wave_sums_store<NV>(acc, sm[w]);
+  } else {
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    double s = acc[i];
-    if (OP == 0) s = wsum(s);
-    else if (OP == 1) s = wmax(s);
-    else s = -wmax(-s);
-    if (lane == 0) sm[w][i] = s;
+    for (int i = 0; i < NV; ++i) {
+      const double s = OP == 1 ? wmax(acc[i]) : -wmax(-acc[i]);
+      if (lane == 0) sm[w][i] = s;
+    }
   }
   __syncthreads();
   if (threadIdx.x < NV) {

@@ -14,6 +14,7 @@
 // it is k_xfwd, k_axis(y, fwd), k_axis(z, fused), k_axis(y, inv), k_xinv.
 #pragma once
 #include "pipeline.h"
+#include "wave.h"
 
 namespace llg {
 
@@ -608,16 +609,7 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
     }
   }
   // block partials of the inner products (fixed order: deterministic)
-  const int lane = tid & 63, wv = tid >> 6;
-#pragma unroll
-  for (int q = 0; q < JB + 2; ++q) {
-    if (q <= J || q == JB + 1) {
-      double s = acc[q];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-      if (lane == 0) dred[wv][q] = s;
-    }
-  }
+  wave_sums_store<JB + 2>(acc, dred[tid >> 6]);
   __syncthreads();
   if (tid <= J + 1) {
     const int src = tid <= J ? tid : JB + 1;
@@ -776,8 +768,7 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
           t = fma(a0, double(keep0[it][f]), fma(a1, double(keep1[it][f]), t));
         }
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+      t = wave_sum(t);
       if (lane == 0) dred[wv][q] = t;
     }
     __syncthreads();
@@ -791,8 +782,7 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
   if (io.red) {
     // block partial of the residual norm or of the energy (fixed order: deterministic)
     __shared__ double rs[C::NT / 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off, 64);
+    rsum = wave_sum(rsum);
     if ((tid & 63) == 0) rs[tid >> 6] = rsum;
     __syncthreads();
     if (tid == 0) {
