@@ -16,8 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libllg.so")
-SOURCES = ["pipeline_f64.hip", "pipeline_f32.hip", "axis.hip", "field.hip", "krylov.hip", "nodal.hip", "noalloc.hip", "xfwd_upd.hip", "profiler.cpp",
-           "capi.cpp"]
+SOURCES = ["pipeline_f64.hip", "pipeline_mixed.hip", "pipeline_f32.hip", "apply_matvec.hip", "field.hip", "krylov.hip",
+           "xfwd_upd.hip", "axis.hip", "nodal.hip", "capi.cpp", "noalloc.hip", "profiler.cpp"]
 ARCH = "gfx950"
 # packed fp32 ops are disabled for every device compile; hipcc's host pass
 # reports the feature as unknown, which is harmless.

@@ -222,13 +222,10 @@ hipError_t op_rhs_low(const Ctx& c, const llg_params* p, const double* m, double
 }
 
 // Number of x-inverse blocks of a float64 pipeline (one residual partial
-// each); the launch shape is XCfg<double, nh> (pipeline_kernels.h).
+// each).
 int xinv_blocks(const Ctx& c) {
-  const int nh = c.geom.nh;
-  const int key = x_plan_key(8, nh);
-  const int tpl = nh / plan_p(key);
-  const int lx = 64 / tpl;
-  return int(((long long)c.ny * c.nz + lx - 1) / lx);
+  const long long lines = (long long)c.ny * c.nz;
+  return int(x_blocks(8, c.geom.nh, lines, x_shape(8, c.geom.nh, lines)));
 }
 
 // r = b - A x in residual form (fused into the operator's last pass); the

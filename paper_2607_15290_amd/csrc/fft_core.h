@@ -326,15 +326,20 @@ __device__ __forceinline__ int stage_in_pos(int t, int slot) {
 
 // Exchange through LDS between stage S-1 and stage S, then compute stage S.
 template <typename T, int KEY, int S, int DIR, class Lds>
-__device__ __forceinline__ void next_stage(cx<T>* v, int t, Lds lds, const cx<T>* __restrict__ tw, int tws) {
+__device__ __forceinline__ void next_stage(cx<T>* v, int t, Lds lds, const cx<T>* __restrict__ tw, int tws,
+                                           bool on) {
   constexpr int P = plan_p(KEY);
   __syncthreads();
+  if (on) {
 #pragma unroll
-  for (int s = 0; s < P; ++s) lds(stage_out_pos<KEY, S - 1>(t, s)) = v[s];
+    for (int s = 0; s < P; ++s) lds(stage_out_pos<KEY, S - 1>(t, s)) = v[s];
+  }
   __syncthreads();
+  if (on) {
 #pragma unroll
-  for (int s = 0; s < P; ++s) v[s] = lds(stage_in_pos<KEY, S>(t, s));
-  stage_compute<T, KEY, S, DIR>(v, t, tw, tws);
+    for (int s = 0; s < P; ++s) v[s] = lds(stage_in_pos<KEY, S>(t, s));
+    stage_compute<T, KEY, S, DIR>(v, t, tw, tws);
+  }
 }
 
 // Full line FFT on registers, exchanging through LDS between stages.
@@ -342,15 +347,17 @@ __device__ __forceinline__ void next_stage(cx<T>* v, int t, Lds lds, const cx<T>
 // Starts with the input pattern (slot in_slot(q) <-> position t + TPL q) and
 // ends with the output pattern (slot s <-> position t + TPL out_q(s)).
 // Contains block barriers when there is more than one stage: every thread of
-// the block must call it the same number of times.
+// the block must call it the same number of times; threads that hold no line
+// (on = false) only take part in the barriers.
 template <typename T, int KEY, int DIR, class Lds>
-__device__ __forceinline__ void line_fft(cx<T>* v, int t, Lds lds, const cx<T>* __restrict__ tw, int tws) {
+__device__ __forceinline__ void line_fft(cx<T>* v, int t, Lds lds, const cx<T>* __restrict__ tw, int tws,
+                                         bool on = true) {
   constexpr int NST = plan_stages(KEY);
   static_assert(plan_ok(KEY), "no FFT plan for this length");
-  stage_compute<T, KEY, 0, DIR>(v, t, tw, tws);
-  if constexpr (NST > 1) next_stage<T, KEY, 1, DIR>(v, t, lds, tw, tws);
-  if constexpr (NST > 2) next_stage<T, KEY, 2, DIR>(v, t, lds, tw, tws);
-  if constexpr (NST > 3) next_stage<T, KEY, 3, DIR>(v, t, lds, tw, tws);
+  if (on) stage_compute<T, KEY, 0, DIR>(v, t, tw, tws);
+  if constexpr (NST > 1) next_stage<T, KEY, 1, DIR>(v, t, lds, tw, tws, on);
+  if constexpr (NST > 2) next_stage<T, KEY, 2, DIR>(v, t, lds, tw, tws, on);
+  if constexpr (NST > 3) next_stage<T, KEY, 3, DIR>(v, t, lds, tw, tws, on);
 }
 
 }  // namespace llg

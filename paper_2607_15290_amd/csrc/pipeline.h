@@ -44,6 +44,36 @@ __host__ __device__ constexpr int x_plan_key(int elem_bytes, int nh) {
   return (elem_bytes == 8 && (nh == 128 || nh == 256)) ? (nh | kPlanFine) : nh;
 }
 
+// Launch shapes of the x passes (rows = x lines per block).  Wide: 192 threads
+// that each hold a part of a line of one of the three fields; streams best
+// when there are several blocks per CU.  Mid and small: 256 threads, some of
+// which only load, store and reduce, on the rows that hold about 256 or 64
+// node pairs, so that grids of few rows still reach every CU.
+enum XShape : int { X_WIDE = 0, X_MID = 1, X_SMALL = 2 };
+__host__ __device__ constexpr int x_lx(int elem_bytes, int nh, int shape) {
+  const int tpl = nh / plan_p(x_plan_key(elem_bytes, nh));
+  if (shape == X_WIDE) return 64 / tpl;
+  const int pairs = shape == X_MID ? 256 : 64, most = 64 / tpl;
+  const int lx = nh >= pairs ? 1 : pairs / nh;
+  return lx < most ? lx : most;
+}
+inline unsigned x_blocks(int elem_bytes, int nh, long long lines, int shape) {
+  const int lx = x_lx(elem_bytes, nh, shape);
+  return unsigned((lines + lx - 1) / lx);
+}
+// Shape of the x passes on a grid: wide above LLG_X_WIDE_BLOCKS wide blocks,
+// otherwise the mid shape if it gives a block to nearly every CU.
+#ifndef LLG_X_WIDE_BLOCKS
+#define LLG_X_WIDE_BLOCKS 256
+#endif
+#ifndef LLG_X_MID_BLOCKS
+#define LLG_X_MID_BLOCKS 192
+#endif
+inline int x_shape(int elem_bytes, int nh, long long lines) {
+  if (x_blocks(elem_bytes, nh, lines, X_WIDE) > LLG_X_WIDE_BLOCKS) return X_WIDE;
+  return x_blocks(elem_bytes, nh, lines, X_MID) >= LLG_X_MID_BLOCKS ? X_MID : X_SMALL;
+}
+
 // FFT plan key of the y / z passes: with LLG_AXIS_FINE_F64 the float64
 // passes at N = 256 take the finer plan as well.
 #ifndef LLG_AXIS_FINE_F64

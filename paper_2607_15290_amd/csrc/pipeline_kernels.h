@@ -21,14 +21,16 @@ namespace llg {
 // Launch shape of the x passes for element type T and half-length NH.  The
 // float64 passes at NH = 128, 256 use the finer plan (8 points per thread):
 // half the lines per block, half the LDS, twice the blocks per CU.
-template <typename T, int NH>
+template <typename T, int NH, int SHAPE = X_WIDE>
 struct XCfg {
   static constexpr int KEY = x_plan_key(int(sizeof(T)), NH);
   static constexpr int P = plan_p(KEY);
   static constexpr int TPL = NH / P;
-  static constexpr int LX = 64 / TPL;           // rows per block
-  static constexpr int NT = 192;                // 3 fields x LX rows x TPL
+  static constexpr int LX = x_lx(int(sizeof(T)), NH, SHAPE);  // rows per block
+  static constexpr int NDFT = 3 * LX * TPL;                    // threads that hold a part of a line
+  static constexpr int NT = SHAPE == X_WIDE ? NDFT : 256;
   static constexpr int SL = NH + (NH >> 4) + 1; // LDS line stride (complex)
+  static_assert(NDFT <= NT, "a block's lines do not fit its threads");
 };
 
 __device__ __forceinline__ int xphys(int pos) { return pos + (pos >> 4); }
@@ -54,6 +56,10 @@ __device__ __forceinline__ int xphys(int pos) { return pos + (pos >> 4); }
 // 6, 200 with 3, 204 with 4)
 #ifndef LLG_XMID_BATCH
 #define LLG_XMID_BATCH LLG_XBATCH_F32
+#endif
+// 16-byte loads per lane in flight in the mid and small shapes's inner products
+#ifndef LLG_DOTS_LOADS
+#define LLG_DOTS_LOADS 16
 #endif
 template <typename U>
 __device__ __forceinline__ U ld_s(const U* p) {
@@ -375,22 +381,27 @@ __device__ __forceinline__ void epilogue_compute(const EpiRaw<T, TIn, TOut, EPI>
 // LDS holds the real node pairs (u[2k], u[2k+1]) of each line at position k:
 // half-length complex DFT, split step U[k] = E[k] + w^k O[k] (E/O the DFTs of
 // the even/odd samples), store of the rows of three half spectra.
-template <typename T, int NH>
+template <typename T, int NH, int SHAPE = X_WIDE>
 __device__ __forceinline__ void x_r2c_store(cx<T>* lds, long long line0, long long nlines,
                                             cx<T>* __restrict__ spec, const SpecGeom& g,
                                             const cx<T>* __restrict__ twx) {
-  using C = XCfg<T, NH>;
+  using C = XCfg<T, NH, SHAPE>;
   const int tid = threadIdx.x;
   const int t = tid % C::TPL, ln = tid / C::TPL;
+  const bool on = C::NDFT == C::NT || tid < C::NDFT;
   cx<T>* line_lds = lds + ln * C::SL;
   auto acc = [line_lds](int pos) -> cx<T>& { return line_lds[xphys(pos)]; };
   cx<T> v[C::P];
+  if (on) {
 #pragma unroll
-  for (int q = 0; q < C::P; ++q) v[in_slot<C::KEY>(q)] = acc(t + C::TPL * q);
-  line_fft<T, C::KEY, -1>(v, t, acc, twx, 2);
+    for (int q = 0; q < C::P; ++q) v[in_slot<C::KEY>(q)] = acc(t + C::TPL * q);
+  }
+  line_fft<T, C::KEY, -1>(v, t, acc, twx, 2, on);
   __syncthreads();
+  if (on) {
 #pragma unroll
-  for (int s = 0; s < C::P; ++s) acc(t + C::TPL * out_q<C::KEY>(s)) = v[s];
+    for (int s = 0; s < C::P; ++s) acc(t + C::TPL * out_q<C::KEY>(s)) = v[s];
+  }
   __syncthreads();
   constexpr int CS = 3 * (NH + 1);
   for (int e = tid; e < C::LX * CS; e += C::NT) {
@@ -413,11 +424,11 @@ __device__ __forceinline__ void x_r2c_store(cx<T>* lds, long long line0, long lo
 // step (Z[k] = (U[k] + conj U[NH-k]) + i w^{-k} (U[k] - conj U[NH-k])) and run
 // the inverse half-length DFT; on return LDS position k of each line holds the
 // node pair (2k, 2k+1) of each field.
-template <typename T, int NH>
+template <typename T, int NH, int SHAPE = X_WIDE>
 __device__ __forceinline__ void x_load_c2r(cx<T>* lds, long long line0, long long nlines,
                                            const cx<T>* __restrict__ spec, const SpecGeom& g,
                                            const cx<T>* __restrict__ twx) {
-  using C = XCfg<T, NH>;
+  using C = XCfg<T, NH, SHAPE>;
   const int tid = threadIdx.x;
   constexpr int CS = 3 * (NH + 1);
   {
@@ -438,34 +449,40 @@ __device__ __forceinline__ void x_load_c2r(cx<T>* lds, long long line0, long lon
   }
   __syncthreads();
   const int t = tid % C::TPL, ln = tid / C::TPL;
+  const bool on = C::NDFT == C::NT || tid < C::NDFT;
   cx<T>* line_lds = lds + ln * C::SL;
   auto acc = [line_lds](int pos) -> cx<T>& { return line_lds[xphys(pos)]; };
   cx<T> v[C::P];
+  if (on) {
 #pragma unroll
-  for (int q = 0; q < C::P; ++q) {
-    const int k = t + C::TPL * q;
-    const cx<T> a = acc(k);
-    const cx<T> bc = acc(NH - k);
-    const cx<T> e{a.x + bc.x, a.y - bc.y};
-    const cx<T> d{a.x - bc.x, a.y + bc.y};
-    const cx<T> o = cmulc(d, twx[k]);
-    v[in_slot<C::KEY>(q)] = {e.x - o.y, e.y + o.x};
+    for (int q = 0; q < C::P; ++q) {
+      const int k = t + C::TPL * q;
+      const cx<T> a = acc(k);
+      const cx<T> bc = acc(NH - k);
+      const cx<T> e{a.x + bc.x, a.y - bc.y};
+      const cx<T> d{a.x - bc.x, a.y + bc.y};
+      const cx<T> o = cmulc(d, twx[k]);
+      v[in_slot<C::KEY>(q)] = {e.x - o.y, e.y + o.x};
+    }
   }
-  line_fft<T, C::KEY, 1>(v, t, acc, twx, 2);
+  line_fft<T, C::KEY, 1>(v, t, acc, twx, 2, on);
   __syncthreads();
+  if (on) {
 #pragma unroll
-  for (int s = 0; s < C::P; ++s) acc(t + C::TPL * out_q<C::KEY>(s)) = v[s];
+    for (int s = 0; s < C::P; ++s) acc(t + C::TPL * out_q<C::KEY>(s)) = v[s];
+  }
   __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
 // k_xfwd
 // ---------------------------------------------------------------------------
-template <typename T, typename TIn, int NH, int PRO>
-__global__ __launch_bounds__(192) void k_xfwd(const TIn* __restrict__ in, const T* __restrict__ m,
-                                              cx<T>* __restrict__ spec, SpecGeom g, NodalArgs na,
-                                              const cx<T>* __restrict__ twx) {
-  using C = XCfg<T, NH>;
+template <typename T, typename TIn, int NH, int PRO, int SHAPE>
+__global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xfwd(const TIn* __restrict__ in,
+                                                                    const T* __restrict__ m,
+                                                                    cx<T>* __restrict__ spec, SpecGeom g,
+                                                                    NodalArgs na, const cx<T>* __restrict__ twx) {
+  using C = XCfg<T, NH, SHAPE>;
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
   const long long nlines = (long long)g.ny * g.nz;
@@ -508,7 +525,7 @@ __global__ __launch_bounds__(192) void k_xfwd(const TIn* __restrict__ in, const 
     }
   }
   __syncthreads();
-  x_r2c_store<T, NH>(lds, line0, nlines, spec, g, twx);
+  x_r2c_store<T, NH, SHAPE>(lds, line0, nlines, spec, g, twx);
 }
 
 // ---------------------------------------------------------------------------
@@ -659,21 +676,29 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
 // Arnoldi basis directions (BasisDots), from the output values it still
 // holds in registers: the separate inner-product pass and its read of the
 // output disappear.
-template <typename T, typename TIn, typename TOut, int NH, int EPI, bool DOTS = false>
-__global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<T>* __restrict__ spec,
-                                              SpecGeom g, NodalArgs na, const cx<T>* __restrict__ twx,
-                                              BasisDots bd) {
+//
+// In the mid and small shapes the output values go to LDS and the block's wavefronts
+// share out the columns: a wavefront reads all of the block's values of its
+// columns, the loads of several columns in flight together, and reduces them
+// alone.  On a cache-resident grid the pass is bound by the latency of its
+// serial chain (load, sum, next column), not by bytes.
+template <typename T, typename TIn, typename TOut, int NH, int EPI, bool DOTS, int SHAPE>
+__global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn, TOut> io,
+                                                                    const cx<T>* __restrict__ spec, SpecGeom g,
+                                                                    NodalArgs na, const cx<T>* __restrict__ twx,
+                                                                    BasisDots bd) {
   static_assert(!DOTS || EPI == EPI_MATVEC || EPI == EPI_FUSED || EPI == EPI_JT_RIGHT,
                 "dots: Krylov output of a matvec or fused pass");
-  using C = XCfg<T, NH>;
+  using C = XCfg<T, NH, SHAPE>;
   __shared__ cx<T> lds[3 * C::LX * C::SL];
+  __shared__ cx<T> lds_o[DOTS && SHAPE != X_WIDE ? 4 * C::LX * NH : 1];  // output pairs, plane-major
   const int tid = threadIdx.x;
   const long long nlines = (long long)g.ny * g.nz;
   const long long line0 = (long long)blockIdx.x * C::LX;
   constexpr int NX = 2 * NH;
   constexpr int CS = 3 * (NH + 1);
 
-  x_load_c2r<T, NH>(lds, line0, nlines, spec, g, twx);
+  x_load_c2r<T, NH, SHAPE>(lds, line0, nlines, spec, g, twx);
 
   // Epilogue: clamped (unconditional) loads issued a batch of node pairs at
   // a time, predicated stores.
@@ -681,7 +706,7 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
   constexpr int NPAIR = C::LX * NH;
   constexpr int ITERS = (NPAIR + C::NT - 1) / C::NT;
   constexpr int BATCH = sizeof(T) == 4 ? LLG_XBATCH_F32 : LLG_XBATCH_F64;
-  constexpr int KEEP = DOTS ? ITERS : 1;
+  constexpr int KEEP = DOTS && SHAPE == X_WIDE ? ITERS : 1;
   T keep0[KEEP][4], keep1[KEEP][4];  // outputs of the thread's node pairs (0 where not live)
 #pragma unroll
   for (int it0 = 0; it0 < ITERS; it0 += BATCH) {
@@ -737,7 +762,12 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
 #pragma unroll
       for (int f = 0; f < NOUT; ++f) store2(io.out + f * io.ng + i, TOut(o0[f]), TOut(o1[f]));
     }
-    if constexpr (DOTS) {
+    if constexpr (DOTS && SHAPE != X_WIDE) {
+      if (e0 < NPAIR) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) lds_o[f * NPAIR + e] = live ? cx<T>{o0[f], o1[f]} : cx<T>{T(0), T(0)};
+      }
+    } else if constexpr (DOTS) {
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
         keep0[it0 + b][f] = live ? o0[f] : T(0);
@@ -746,7 +776,45 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
     }
   }
   }
-  if constexpr (DOTS) {
+  if constexpr (DOTS && SHAPE != X_WIDE) {
+    __syncthreads();
+    constexpr int NW = C::NT / 64, NITEM = 4 * NPAIR, NIT = (NITEM + 63) / 64;
+    constexpr int QB = NIT >= LLG_DOTS_LOADS ? 1 : (LLG_DOTS_LOADS / NIT > 8 ? 8 : LLG_DOTS_LOADS / NIT);
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    cx<T> w[NIT];
+    long long off[NIT];
+#pragma unroll
+    for (int i = 0; i < NIT; ++i) {
+      const int it0 = lane + 64 * i;
+      const int it = it0 < NITEM ? it0 : NITEM - 1;
+      const int f = it / NPAIR, e = it % NPAIR;
+      const int l = e / NH, xp = e % NH;
+      const long long line = line0 + l < nlines ? line0 + l : nlines - 1;
+      off[i] = f * io.ng + line * NX + 2 * xp;
+      w[i] = it0 < NITEM ? lds_o[it] : cx<T>{T(0), T(0)};
+    }
+    for (int q0 = wv; q0 < bd.nv; q0 += NW * QB) {
+      double a0[QB][NIT], a1[QB][NIT];
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        const int q = q0 + k * NW < bd.nv ? q0 + k * NW : q0;
+        const double* col = q == 0 ? bd.u0 : bd.U1 + (q - 1) * bd.ld;
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) load2(col + off[i], a0[k][i], a1[k][i]);
+      }
+      double t[QB];
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        t[k] = 0.0;
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) t[k] = fma(a0[k][i], double(w[i].x), fma(a1[k][i], double(w[i].y), t[k]));
+      }
+      const double s = wave_sums<QB>(t);
+      const int k = wave_sums_index<QB>(lane), q = q0 + k * NW;
+      if ((lane & (64 / wave_pow2(QB) - 1)) == 0 && k < QB && q < bd.nv)
+        bd.partial[(long long)q * gridDim.x + blockIdx.x] = s;
+    }
+  } else if constexpr (DOTS) {
     // u_q . out for q < nv: per column, the clamped (unconditional) loads of
     // all the thread's node pairs are in flight together; dead pairs weigh 0.
     __shared__ double dred[C::NT / 64][kBasisDotsMax];
@@ -803,17 +871,19 @@ __global__ __launch_bounds__(192) void k_xinv(PipeIO<T, TIn, TOut> io, const cx<
 // is owned by one thread, which reads the apply's field from an LDS slot and
 // writes z back into the same slot.
 // ---------------------------------------------------------------------------
-template <int NH>
-__global__ __launch_bounds__(192) void k_xmid(PipeIO<float, double, float> io, cx<float>* __restrict__ spec,
-                                              SpecGeom g, NodalArgs na, const cx<float>* __restrict__ twx) {
+template <int NH, int SHAPE>
+__global__ __launch_bounds__((XCfg<float, NH, SHAPE>::NT)) void k_xmid(PipeIO<float, double, float> io,
+                                                                        cx<float>* __restrict__ spec, SpecGeom g,
+                                                                        NodalArgs na,
+                                                                        const cx<float>* __restrict__ twx) {
   using T = float;
-  using C = XCfg<T, NH>;
+  using C = XCfg<T, NH, SHAPE>;
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
   const long long nlines = (long long)g.ny * g.nz;
   const long long line0 = (long long)blockIdx.x * C::LX;
   constexpr int NX = 2 * NH;
-  x_load_c2r<T, NH>(lds, line0, nlines, spec, g, twx);
+  x_load_c2r<T, NH, SHAPE>(lds, line0, nlines, spec, g, twx);
 
   constexpr int NPAIR = C::LX * NH;
   constexpr int ITERS = (NPAIR + C::NT - 1) / C::NT;
@@ -860,7 +930,7 @@ __global__ __launch_bounds__(192) void k_xmid(PipeIO<float, double, float> io, c
     }
   }
   __syncthreads();
-  x_r2c_store<T, NH>(lds, line0, nlines, spec, g, twx);
+  x_r2c_store<T, NH, SHAPE>(lds, line0, nlines, spec, g, twx);
 }
 
 // ---------------------------------------------------------------------------

@@ -2,6 +2,8 @@
 // Included by the per-precision translation units, which instantiate
 // run_pipeline for the type combinations they need.
 #pragma once
+#include <type_traits>
+
 #include "llg_internal.h"
 #include "krylov.h"
 #include "pipeline_kernels.h"
@@ -28,18 +30,34 @@ constexpr bool has_epi(int epi) {
   else return epi == EPI_MATVEC;
 }
 
+// Calls f(integral_constant shape, blocks, threads) with the x passes' launch
+// shape on this grid (x_shape).
+template <typename T, int NH, int SHAPE, class F>
+void x_launch(long long lines, F&& f) {
+  f(std::integral_constant<int, SHAPE>{}, x_blocks(int(sizeof(T)), NH, lines, SHAPE),
+    unsigned(XCfg<T, NH, SHAPE>::NT));
+}
+template <typename T, int NH, class F>
+void with_x_shape(long long lines, F&& f) {
+  switch (x_shape(int(sizeof(T)), NH, lines)) {
+    case X_WIDE: x_launch<T, NH, X_WIDE>(lines, f); break;
+    case X_MID: x_launch<T, NH, X_MID>(lines, f); break;
+    default: x_launch<T, NH, X_SMALL>(lines, f); break;
+  }
+}
+
 template <typename T, typename TIn, typename TOut, int NH, int PRO>
 void launch_xfwd(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& io, hipStream_t st) {
   if constexpr (has_pro<T, TIn, TOut>(PRO)) {
-    using C = XCfg<T, NH>;
     const long long lines = (long long)c.ny * c.nz;
-    const unsigned grid = (unsigned)((lines + C::LX - 1) / C::LX);
     const cx<T>* tw;
     if constexpr (std::is_same<T, double>::value) tw = c.tw_d[0]; else tw = c.tw_f[0];
     const double in_b = PRO == PRO_COPY3 ? 3.0 * sizeof(TIn) : 4.0 * sizeof(TIn) + 3.0 * sizeof(T);
     ProfScope ps(c.prof, st, KK_XFWD, double(c.ng) * in_b + double(c.geom.cs) * lines * 2 * sizeof(T));
-    hipLaunchKernelGGL((k_xfwd<T, TIn, NH, PRO>), dim3(grid), dim3(C::NT), 0, st, io.in, io.m,
-                       reinterpret_cast<cx<T>*>(c.spec), c.geom, na, tw);
+    with_x_shape<T, NH>(lines, [&](auto shape, unsigned grid, unsigned nt) {
+      hipLaunchKernelGGL((k_xfwd<T, TIn, NH, PRO, decltype(shape)::value>), dim3(grid), dim3(nt), 0, st, io.in, io.m,
+                         reinterpret_cast<cx<T>*>(c.spec), c.geom, na, tw);
+    });
   }
 }
 
@@ -62,15 +80,15 @@ double xinv_node_bytes(const NodalArgs& na, const PipeIO<T, TIn, TOut>& io) {
 template <typename T, typename TIn, typename TOut, int NH, int EPI>
 void launch_xinv(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& io, hipStream_t st) {
   if constexpr (has_epi<T, TIn, TOut>(EPI)) {
-    using C = XCfg<T, NH>;
     const long long lines = (long long)c.ny * c.nz;
-    const unsigned grid = (unsigned)((lines + C::LX - 1) / C::LX);
     const cx<T>* tw;
     if constexpr (std::is_same<T, double>::value) tw = c.tw_d[0]; else tw = c.tw_f[0];
     const double node_b = xinv_node_bytes<T, TIn, TOut, EPI>(na, io);
     ProfScope ps(c.prof, st, KK_XINV, double(c.ng) * node_b + double(c.geom.cs) * lines * 2 * sizeof(T));
-    hipLaunchKernelGGL((k_xinv<T, TIn, TOut, NH, EPI>), dim3(grid), dim3(C::NT), 0, st, io,
-                       reinterpret_cast<const cx<T>*>(c.spec), c.geom, na, tw, BasisDots{});
+    with_x_shape<T, NH>(lines, [&](auto shape, unsigned grid, unsigned nt) {
+      hipLaunchKernelGGL((k_xinv<T, TIn, TOut, NH, EPI, false, decltype(shape)::value>), dim3(grid), dim3(nt), 0, st,
+                         io, reinterpret_cast<const cx<T>*>(c.spec), c.geom, na, tw, BasisDots{});
+    });
   }
 }
 
@@ -79,10 +97,9 @@ void launch_xinv(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& 
 template <typename T, typename TIn, typename TOut, int NH, int EPI>
 hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& io, const BasisDots& bd,
                             double* dots_out, hipStream_t st) {
-  using C = XCfg<T, NH>;
   if (bd.nv < 1 || bd.nv > kBasisDotsMax || io.rhs) return hipErrorInvalidValue;
   const long long lines = (long long)c.ny * c.nz;
-  const unsigned grid = (unsigned)((lines + C::LX - 1) / C::LX);
+  const unsigned grid = x_blocks(int(sizeof(T)), NH, lines, x_shape(int(sizeof(T)), NH, lines));
   if (bd.defer_nb) *bd.defer_nb = 0;
   if (grid > (unsigned)kRedBlocksMax) {
     // more blocks than partial rows (the largest grids in float64): plain
@@ -103,8 +120,10 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
   {
     const double node_b = xinv_node_bytes<T, TIn, TOut, EPI>(na, io) + 4.0 * 8 * bd.nv;
     ProfScope ps(c.prof, st, KK_XINV_DOTS, double(c.ng) * node_b + double(c.geom.cs) * lines * 2 * sizeof(T));
-    hipLaunchKernelGGL((k_xinv<T, TIn, TOut, NH, EPI, true>), dim3(grid), dim3(C::NT), 0, st, io,
-                       reinterpret_cast<const cx<T>*>(c.spec), c.geom, na, tw, kd);
+    with_x_shape<T, NH>(lines, [&](auto shape, unsigned blocks, unsigned nt) {
+      hipLaunchKernelGGL((k_xinv<T, TIn, TOut, NH, EPI, true, decltype(shape)::value>), dim3(blocks), dim3(nt), 0,
+                         st, io, reinterpret_cast<const cx<T>*>(c.spec), c.geom, na, tw, kd);
+    });
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -192,7 +211,6 @@ template <int NH, typename TW>
 hipError_t run_apply_matvec_nh(const Ctx& c, const SymArgs& sym_ap, const SymArgs& sym_mv, const NodalArgs& na,
                                const double* v, const float* m32, float* z, TW* w, const BasisDots* bd,
                                double* dots_out, bool spec_ready, hipStream_t st) {
-  using C = XCfg<float, NH>;
   PipeIO<float, double, float> io_ap{v, m32, z, c.ng, nullptr, nullptr};
   PipeIO<float, float, TW> io_mv{z, m32, w, c.ng, nullptr, nullptr};
   if (!spec_ready) launch_xfwd<float, double, float, NH, PRO_COPY3>(c, na, io_ap, st);
@@ -200,11 +218,12 @@ hipError_t run_apply_matvec_nh(const Ctx& c, const SymArgs& sym_ap, const SymArg
   if ((e = run_axes<float>(c, sym_ap, st)) != hipSuccess) return e;
   {
     const long long lines = (long long)c.ny * c.nz;
-    const unsigned grid = (unsigned)((lines + C::LX - 1) / C::LX);
     const double bytes = 2.0 * double(c.geom.cs) * lines * sizeof(cx<float>) + double(c.ng) * (8.0 + 12.0 + 16.0);
     ProfScope ps(c.prof, st, KK_XMID, bytes);
-    hipLaunchKernelGGL((k_xmid<NH>), dim3(grid), dim3(C::NT), 0, st, io_ap, reinterpret_cast<cx<float>*>(c.spec),
-                       c.geom, na, c.tw_f[0]);
+    with_x_shape<float, NH>(lines, [&](auto shape, unsigned grid, unsigned nt) {
+      hipLaunchKernelGGL((k_xmid<NH, decltype(shape)::value>), dim3(grid), dim3(nt), 0, st, io_ap,
+                         reinterpret_cast<cx<float>*>(c.spec), c.geom, na, c.tw_f[0]);
+    });
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = run_axes<float>(c, sym_mv, st)) != hipSuccess) return e;
