@@ -26,17 +26,25 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Non-temporal 16-byte load / store: the Krylov vectors (hundreds of MB each)
-// are streamed once per pass and never reused from cache before eviction.
+// 16-byte load / store of a Krylov vector, with the non-temporal hint (NT)
+// where the vectors are streamed (hundreds of MB each, never reused from cache
+// before eviction) and without it on grids whose basis stays in the caches.
+template <bool NT = true>
 __device__ __forceinline__ double2 ldnt(const double2* p) {
+  if constexpr (!NT) return *p;
   double2 v;
   v.x = __builtin_nontemporal_load(&p->x);
   v.y = __builtin_nontemporal_load(&p->y);
   return v;
 }
+template <bool NT = true>
 __device__ __forceinline__ void stnt(double2* p, double2 v) {
-  __builtin_nontemporal_store(v.x, &p->x);
-  __builtin_nontemporal_store(v.y, &p->y);
+  if constexpr (!NT) {
+    *p = v;
+  } else {
+    __builtin_nontemporal_store(v.x, &p->x);
+    __builtin_nontemporal_store(v.y, &p->y);
+  }
 }
 // The operator output w of an Arnoldi step, as a pair of float64 values: a
 // float64 vector, or the float32 output of the precision form's operators
@@ -366,16 +374,16 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n2; e += stride) {
     double2 se = ldw(w + e);
     double2 q[J + 1];
-    q[0] = ldnt(u0 + e);
+    q[0] = ldnt<!COEF>(u0 + e);
 #pragma unroll
-    for (int i = 1; i <= J; ++i) q[i] = ldnt(U1 + (i - 1) * ld2 + e);
+    for (int i = 1; i <= J; ++i) q[i] = ldnt<!COEF>(U1 + (i - 1) * ld2 + e);
 #pragma unroll
     for (int i = 0; i <= J; ++i) {
       se.x = fma(-gm[i], q[i].x, se.x);
       se.y = fma(-gm[i], q[i].y, se.y);
     }
     const double2 un{se.x * inv_beta, se.y * inv_beta};
-    stnt(unew + e, un);
+    stnt<!COEF>(unew + e, un);
 #pragma unroll
     for (int i = 0; i <= J; ++i) acc[i] = fma(q[i].x, un.x, fma(q[i].y, un.y, acc[i]));
     acc[J + 1] = fma(un.x, un.x, fma(un.y, un.y, acc[J + 1]));

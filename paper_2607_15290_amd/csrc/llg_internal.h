@@ -100,10 +100,16 @@ void scratch_setup(int device);
 // in the pipeline_*.hip translation units.
 // With bd (bd->nv > 0; fused M^{-1} A passes with a float64 output only) the
 // last pass also leaves the Arnoldi inner products u_q . out in dots_out.
+template <typename T, typename TIn, typename TOut, bool HI>
+hipError_t run_pipeline_part(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
+                             const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd, double* dots_out);
 template <typename T, typename TIn, typename TOut>
 hipError_t run_pipeline(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
                         const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd = nullptr,
-                        double* dots_out = nullptr);
+                        double* dots_out = nullptr) {
+  if (c.geom.nh <= kNhLoMax) return run_pipeline_part<T, TIn, TOut, false>(c, pro, epi, sym, na, io, st, bd, dots_out);
+  return run_pipeline_part<T, TIn, TOut, true>(c, pro, epi, sym, na, io, st, bd, dots_out);
+}
 
 // Precision-form inner operator (pipeline_f32.hip): z = M^{-1} v (float32,
 // stored) and w = A z (float32, float64 result), the two pipelines joined by

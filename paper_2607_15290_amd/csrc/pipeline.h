@@ -30,9 +30,10 @@ namespace llg {
 
 // Line lengths with kernel instantiations: half-lengths nx/2 of the x passes
 // and lengths of the y / z passes (plans in fft_core.h).
-#define LLG_FOR_NH(X) \
-  X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(128) \
-  X(160) X(192) X(256)
+#define LLG_FOR_NH_LO(X) X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32)
+#define LLG_FOR_NH_HI(X) X(40) X(48) X(64) X(80) X(96) X(128) X(160) X(192) X(256)
+#define LLG_FOR_NH(X) LLG_FOR_NH_LO(X) LLG_FOR_NH_HI(X)
+constexpr int kNhLoMax = 32;  // the pipelines of the two halves are separate translation units
 #define LLG_FOR_AXIS(X) \
   X(4) X(6) X(8) X(10) X(12) X(16) X(20) X(24) X(32) X(40) X(48) X(64) X(80) X(96) X(128) X(160) X(192) \
   X(256) X(320) X(384) X(512)

@@ -36,13 +36,14 @@ struct XCfg {
 __device__ __forceinline__ int xphys(int pos) { return pos + (pos >> 4); }
 
 // Grid planes (inputs, magnetization, outputs) are streamed with non-temporal
-// hints: each is touched once per pipeline and is far larger than the caches.
-// The spectral buffer is accessed with ordinary (cacheable) loads and stores:
-// it is reused by the next pass, and in float32 (about 200 MB at 256^3) much
-// of it stays in the 256 MB Infinity Cache between passes.
-#ifndef LLG_PIPE_NT
-#define LLG_PIPE_NT 1
-#endif
+// hints (NT) by the wide passes: each plane is touched once per pipeline and
+// is far larger than the caches.  The other shapes run on grids whose planes
+// and basis stay in the L2s and the Infinity Cache, where the hint costs
+// (512^2 midpoint steps 10.8 ms with it, 9.6 ms without), so they load and
+// store without.  The spectral buffer always takes ordinary accesses: it is
+// reused by the next pass, and in float32 (about 200 MB at 256^3) much of it
+// stays in the 256 MB Infinity Cache between passes.
+__host__ __device__ constexpr bool x_nt(int shape) { return shape == X_WIDE; }
 // Node pairs per thread whose plane loads are issued together in the x passes
 // (float32: 6, about 4% faster x-forward at 256^3 than 3; float64: 3, the
 // larger batch costs occupancy).
@@ -57,49 +58,30 @@ __device__ __forceinline__ int xphys(int pos) { return pos + (pos >> 4); }
 #ifndef LLG_XMID_BATCH
 #define LLG_XMID_BATCH LLG_XBATCH_F32
 #endif
-// 16-byte loads per lane in flight in the mid and small shapes's inner products
+// 16-byte loads per lane in flight in the mid and small shapes' inner products
 #ifndef LLG_DOTS_LOADS
 #define LLG_DOTS_LOADS 16
 #endif
-template <typename U>
-__device__ __forceinline__ U ld_s(const U* p) {
-#if LLG_PIPE_NT
-  return __builtin_nontemporal_load(p);
-#else
-  return *p;
-#endif
-}
-template <typename U>
-__device__ __forceinline__ void st_s(U* p, U v) {
-#if LLG_PIPE_NT
-  __builtin_nontemporal_store(v, p);
-#else
-  *p = v;
-#endif
-}
-
-template <typename U>
+template <bool NT, typename U>
 __device__ __forceinline__ void load2(const U* __restrict__ p, U& a, U& b) {
-  a = ld_s(p);
-  b = ld_s(p + 1);
+  if constexpr (NT) {
+    a = __builtin_nontemporal_load(p);
+    b = __builtin_nontemporal_load(p + 1);
+  } else {
+    a = p[0];
+    b = p[1];
+  }
 }
 
-template <typename U>
+template <bool NT, typename U>
 __device__ __forceinline__ void store2(U* __restrict__ p, U a, U b) {
-  st_s(p, a);
-  st_s(p + 1, b);
-}
-
-// Pair access at a wave-uniform plane base plus a 32-bit per-lane byte
-// offset: the load takes the scalar-base address form, so a pass touching
-// many planes keeps one offset register instead of a 64-bit address per plane.
-template <typename U>
-__device__ __forceinline__ void load2_at(const U* __restrict__ base, unsigned boff, U& a, U& b) {
-  load2(reinterpret_cast<const U*>(reinterpret_cast<const char*>(base) + boff), a, b);
-}
-template <typename U>
-__device__ __forceinline__ void store2_at(U* __restrict__ base, unsigned boff, U a, U b) {
-  store2(reinterpret_cast<U*>(reinterpret_cast<char*>(base) + boff), a, b);
+  if constexpr (NT) {
+    __builtin_nontemporal_store(a, p);
+    __builtin_nontemporal_store(b, p + 1);
+  } else {
+    p[0] = a;
+    p[1] = b;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -152,14 +134,14 @@ struct ProRaw {
   T m[NM > 0 ? NM : 1][2];
 };
 
-template <typename T, typename TIn, int PRO>
+template <bool NT, typename T, typename TIn, int PRO>
 __device__ __forceinline__ void prologue_load(const TIn* __restrict__ in, const T* __restrict__ m, long long ng,
                                               long long i, ProRaw<T, TIn, PRO>& r) {
   using R = ProRaw<T, TIn, PRO>;
 #pragma unroll
-  for (int f = 0; f < R::NV; ++f) load2(in + f * ng + i, r.v[f][0], r.v[f][1]);
+  for (int f = 0; f < R::NV; ++f) load2<NT>(in + f * ng + i, r.v[f][0], r.v[f][1]);
 #pragma unroll
-  for (int f = 0; f < R::NM; ++f) load2(m + f * ng + i, r.m[f][0], r.m[f][1]);
+  for (int f = 0; f < R::NM; ++f) load2<NT>(m + f * ng + i, r.m[f][0], r.m[f][1]);
 }
 
 template <typename T, typename TIn, int PRO>
@@ -211,7 +193,7 @@ struct EpiRaw {
   TOut rb[4][2];    // right-hand side (residual form)
 };
 
-template <typename T, typename TIn, typename TOut, int EPI>
+template <bool NT, typename T, typename TIn, typename TOut, int EPI>
 __device__ __forceinline__ void epilogue_load(const PipeIO<T, TIn, TOut>& io, const NodalArgs& na, long long i,
                                               EpiRaw<T, TIn, TOut, EPI>& r) {
   const long long ng = io.ng;
@@ -220,32 +202,32 @@ __device__ __forceinline__ void epilogue_load(const PipeIO<T, TIn, TOut>& io, co
     constexpr bool ONLY_R = EPI == EPI_APPLY || EPI == EPI_APPLY_SYM;
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
-      if (!ONLY_R || f == 3) load2(io.in + f * ng + i, r.v[f][0], r.v[f][1]);
+      if (!ONLY_R || f == 3) load2<NT>(io.in + f * ng + i, r.v[f][0], r.v[f][1]);
       else r.v[f][0] = r.v[f][1] = TIn(0);
     }
     if constexpr (EPI != EPI_APPLY_SYM) {
 #pragma unroll
-      for (int f = 0; f < 3; ++f) load2(io.m + f * ng + i, r.m[f][0], r.m[f][1]);
+      for (int f = 0; f < 3; ++f) load2<NT>(io.m + f * ng + i, r.m[f][0], r.m[f][1]);
     } else {
 #pragma unroll
       for (int f = 0; f < 3; ++f) r.m[f][0] = r.m[f][1] = T(0);
     }
     if constexpr (EPI == EPI_JT || EPI == EPI_JT_RIGHT) {
 #pragma unroll
-      for (int f = 0; f < 3; ++f) load2(io.aux_v + f * ng + i, r.av[f][0], r.av[f][1]);
-      load2(io.aux_r + i, r.ar[0], r.ar[1]);
+      for (int f = 0; f < 3; ++f) load2<NT>(io.aux_v + f * ng + i, r.av[f][0], r.av[f][1]);
+      load2<NT>(io.aux_r + i, r.ar[0], r.ar[1]);
     }
   } else if constexpr (EPI == EPI_ADDF) {
 #pragma unroll
-    for (int f = 0; f < 3; ++f) load2(io.aux_v + f * ng + i, r.av[f][0], r.av[f][1]);
+    for (int f = 0; f < 3; ++f) load2<NT>(io.aux_v + f * ng + i, r.av[f][0], r.av[f][1]);
   } else if constexpr (EPI == EPI_RHS || EPI == EPI_ENERGY) {
     if constexpr (EPI == EPI_ENERGY) {
 #pragma unroll
-      for (int f = 0; f < 3; ++f) load2(io.m + f * ng + i, r.m[f][0], r.m[f][1]);
+      for (int f = 0; f < 3; ++f) load2<NT>(io.m + f * ng + i, r.m[f][0], r.m[f][1]);
     }
     if (na.hfield) {
 #pragma unroll
-      for (int f = 0; f < 3; ++f) load2(na.hfield + f * ng + i, r.hf[f][0], r.hf[f][1]);
+      for (int f = 0; f < 3; ++f) load2<NT>(na.hfield + f * ng + i, r.hf[f][0], r.hf[f][1]);
     } else {
 #pragma unroll
       for (int f = 0; f < 3; ++f) r.hf[f][0] = r.hf[f][1] = 0.0;
@@ -254,7 +236,7 @@ __device__ __forceinline__ void epilogue_load(const PipeIO<T, TIn, TOut>& io, co
   if (io.rhs) {
     constexpr int NOUT = EPI == EPI_STORE3 ? 3 : 4;
 #pragma unroll
-    for (int f = 0; f < NOUT; ++f) load2(io.rhs + f * ng + i, r.rb[f][0], r.rb[f][1]);
+    for (int f = 0; f < NOUT; ++f) load2<NT>(io.rhs + f * ng + i, r.rb[f][0], r.rb[f][1]);
   }
 }
 
@@ -483,6 +465,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xfwd(const TIn* __
                                                                     cx<T>* __restrict__ spec, SpecGeom g,
                                                                     NodalArgs na, const cx<T>* __restrict__ twx) {
   using C = XCfg<T, NH, SHAPE>;
+  constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
   const long long nlines = (long long)g.ny * g.nz;
@@ -505,7 +488,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xfwd(const TIn* __
         const int e = e0 < NPAIR ? e0 : NPAIR - 1;
         const int l = e / NH, xp = e % NH;
         const long long line = line0 + l < nlines ? line0 + l : nlines - 1;
-        prologue_load<T, TIn, PRO>(in, m, g.ng, line * NX + 2 * xp, raw[b]);
+        prologue_load<NT, T, TIn, PRO>(in, m, g.ng, line * NX + 2 * xp, raw[b]);
       }
     }
 #pragma unroll
@@ -553,6 +536,7 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
                                                   cx<T>* __restrict__ spec, SpecGeom g, NodalArgs na,
                                                   const cx<T>* __restrict__ twx) {
   using C = XCfg<T, NH>;
+  constexpr bool NT = true;
   constexpr bool NODAL = PRO != PRO_COPY3;  // the prologue needs all four planes and m
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   __shared__ cx<T> lds_r[NODAL ? C::LX * NH : 1];  // plane 3 of u_new (nodal prologues)
@@ -593,12 +577,12 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
       // LDS destination: DFT slot of field f, or (plane 3) the parking row
       slot[b] = tt >= NITEM ? -1 : (f < 3 ? (f * C::LX + l) * C::SL + xphys(xp) : -2 - e);
       W w0, w1;
-      load2(w + k[b], w0, w1);
+      load2<NT>(w + k[b], w0, w1);
       s0[b] = double(w0);
       s1[b] = double(w1);
 #pragma unroll
       for (int q = 0; q <= JB; ++q) {
-        if (q <= J) load2((q == 0 ? ua.u0 : ua.U1 + (q - 1) * ua.ld) + k[b], q0[b][q], q1[b][q]);
+        if (q <= J) load2<NT>((q == 0 ? ua.u0 : ua.U1 + (q - 1) * ua.ld) + k[b], q0[b][q], q1[b][q]);
       }
     }
 #pragma unroll
@@ -611,7 +595,7 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
         }
       }
       const double a0 = s0[b] * ua.inv_beta, a1 = s1[b] * ua.inv_beta;
-      if (live[b]) store2(ua.unew + k[b], a0, a1);
+      if (live[b]) store2<NT>(ua.unew + k[b], a0, a1);
       const double d0 = live[b] ? a0 : 0.0, d1 = live[b] ? a1 : 0.0;
 #pragma unroll
       for (int q = 0; q <= JB; ++q) {
@@ -648,7 +632,7 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
         const long long i = (live ? line0 + l : line0) * NX + 2 * xp;
         ProRaw<T, T, PRO> raw;
 #pragma unroll
-        for (int f = 0; f < 3; ++f) load2(m + f * g.ng + i, raw.m[f][0], raw.m[f][1]);
+        for (int f = 0; f < 3; ++f) load2<NT>(m + f * g.ng + i, raw.m[f][0], raw.m[f][1]);
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
           const cx<T> v = lds[(f * C::LX + l) * C::SL + xphys(xp)];
@@ -690,6 +674,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
   static_assert(!DOTS || EPI == EPI_MATVEC || EPI == EPI_FUSED || EPI == EPI_JT_RIGHT,
                 "dots: Krylov output of a matvec or fused pass");
   using C = XCfg<T, NH, SHAPE>;
+  constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   __shared__ cx<T> lds_o[DOTS && SHAPE != X_WIDE ? 4 * C::LX * NH : 1];  // output pairs, plane-major
   const int tid = threadIdx.x;
@@ -718,7 +703,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
       const int e = e0 < NPAIR ? e0 : NPAIR - 1;
       const int l = e / NH, xp = e % NH;
       const long long line = line0 + l < nlines ? line0 + l : nlines - 1;
-      epilogue_load<T, TIn, TOut, EPI>(io, na, line * NX + 2 * xp, raw[b]);
+      epilogue_load<NT, T, TIn, TOut, EPI>(io, na, line * NX + 2 * xp, raw[b]);
     }
   }
 #pragma unroll
@@ -743,7 +728,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
     if constexpr (EPI == EPI_RHS) {
       if (io.out_f && live) {
 #pragma unroll
-        for (int f = 0; f < 3; ++f) store2(io.out_f + f * io.ng + i, fz[f].x, fz[f].y);
+        for (int f = 0; f < 3; ++f) store2<NT>(io.out_f + f * io.ng + i, fz[f].x, fz[f].y);
       }
     }
     constexpr int NOUT = EPI == EPI_STORE3 ? 3 : (EPI == EPI_ENERGY ? 0 : 4);
@@ -760,7 +745,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
     }
     if (live) {
 #pragma unroll
-      for (int f = 0; f < NOUT; ++f) store2(io.out + f * io.ng + i, TOut(o0[f]), TOut(o1[f]));
+      for (int f = 0; f < NOUT; ++f) store2<NT>(io.out + f * io.ng + i, TOut(o0[f]), TOut(o1[f]));
     }
     if constexpr (DOTS && SHAPE != X_WIDE) {
       if (e0 < NPAIR) {
@@ -800,7 +785,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
         const int q = q0 + k * NW < bd.nv ? q0 + k * NW : q0;
         const double* col = q == 0 ? bd.u0 : bd.U1 + (q - 1) * bd.ld;
 #pragma unroll
-        for (int i = 0; i < NIT; ++i) load2(col + off[i], a0[k][i], a1[k][i]);
+        for (int i = 0; i < NIT; ++i) load2<NT>(col + off[i], a0[k][i], a1[k][i]);
       }
       double t[QB];
 #pragma unroll
@@ -832,7 +817,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
           double a0, a1;
-          load2(col + f * io.ng + i, a0, a1);
+          load2<NT>(col + f * io.ng + i, a0, a1);
           t = fma(a0, double(keep0[it][f]), fma(a1, double(keep1[it][f]), t));
         }
       }
@@ -878,6 +863,7 @@ __global__ __launch_bounds__((XCfg<float, NH, SHAPE>::NT)) void k_xmid(PipeIO<fl
                                                                         const cx<float>* __restrict__ twx) {
   using T = float;
   using C = XCfg<T, NH, SHAPE>;
+  constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
   const long long nlines = (long long)g.ny * g.nz;
@@ -898,7 +884,7 @@ __global__ __launch_bounds__((XCfg<float, NH, SHAPE>::NT)) void k_xmid(PipeIO<fl
         const int e = e0 < NPAIR ? e0 : NPAIR - 1;
         const int l = e / NH, xp = e % NH;
         const long long line = line0 + l < nlines ? line0 + l : nlines - 1;
-        epilogue_load<T, double, T, EPI_APPLY>(io, na, line * NX + 2 * xp, raw[b]);
+        epilogue_load<NT, T, double, T, EPI_APPLY>(io, na, line * NX + 2 * xp, raw[b]);
       }
     }
 #pragma unroll
@@ -922,7 +908,7 @@ __global__ __launch_bounds__((XCfg<float, NH, SHAPE>::NT)) void k_xmid(PipeIO<fl
       }
       if (live) {
 #pragma unroll
-        for (int f = 0; f < 4; ++f) store2(io.out + f * io.ng + i, o0[f], o1[f]);
+        for (int f = 0; f < 4; ++f) store2<NT>(io.out + f * io.ng + i, o0[f], o1[f]);
       }
 #pragma unroll
       for (int f = 0; f < 3; ++f)

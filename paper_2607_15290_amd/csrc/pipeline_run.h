@@ -236,16 +236,24 @@ hipError_t run_apply_matvec_nh(const Ctx& c, const SymArgs& sym_ap, const SymArg
   return launch_xinv_dots<float, float, TW, NH, EPI_MATVEC>(c, na, io_mv, *bd, dots_out, st);
 }
 
-template <typename T, typename TIn, typename TOut>
-hipError_t run_pipeline(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
-                        const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd, double* dots_out) {
-  switch (c.geom.nh) {
+// run_pipeline on the half-lengths of one list (HI: above kNhLoMax).
+template <typename T, typename TIn, typename TOut, bool HI>
+hipError_t run_pipeline_part(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
+                             const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd, double* dots_out) {
 #define LLG_CASE(n) \
   case n: return run_nh<T, TIn, TOut, n>(c, pro, epi, sym, na, io, st, bd, dots_out);
-    LLG_FOR_NH(LLG_CASE)
-#undef LLG_CASE
-    default: return hipErrorInvalidValue;
+  if constexpr (HI) {
+    switch (c.geom.nh) { LLG_FOR_NH_HI(LLG_CASE) }
+  } else {
+    switch (c.geom.nh) { LLG_FOR_NH_LO(LLG_CASE) }
   }
+#undef LLG_CASE
+  return hipErrorInvalidValue;
 }
+
+#define LLG_PIPELINE_PART(T, TIn, TOut, HI)                                                                   \
+  template hipError_t run_pipeline_part<T, TIn, TOut, HI>(const Ctx&, int, int, const SymArgs&,               \
+                                                          const NodalArgs&, const PipeIO<T, TIn, TOut>&,      \
+                                                          hipStream_t, const BasisDots*, double*);
 
 }  // namespace llg

@@ -63,7 +63,7 @@ def test_products_in_every_shape(shape, nb):
     z = torch.empty((4, nz, ny, nx), dtype=torch.float32, device="cuda:0")
     y, dots = P.llg_precond_op_f32(ctx, prm, mf, dev(x), side=1, z=z, basis=basis)
     lev = sum(2 * int(np.ceil(np.log2(n))) for n in (nx, ny, nz) if n > 1) + 16
-    zr = operators.hss_apply(g, op, host(mf), x)
+    zr = operators.hss_apply(g, op, host(mf), x.astype(np.float32).astype(np.float64))
     assert_elem(host(z), zr, lev * 2.0 ** -24, "z float32")
     check_dots(y, dots, "flexible float32")
     ctx.close()
