@@ -244,11 +244,10 @@ ResidOp resid_op(const Ctx& c, int epi, const SymArgs& sym, const NodalArgs& na,
   };
 }
 
-// Read n doubles of device memory (after the stream's queued work).
+// The n values that the stream's latest reduction posted from the slots at dev.
 llg_status fetch(const Ctx& c, const double* dev, int n, hipStream_t st, double* host_out) {
-  CHK(hipMemcpyAsync(c.host, dev, sizeof(double) * n, hipMemcpyDeviceToHost, st));
-  CHK(hipStreamSynchronize(st));
-  std::memcpy(host_out, c.host, sizeof(double) * n);
+  CHK(await_post(c, st));
+  std::memcpy(host_out, c.hmirror + (dev - c.dots), sizeof(double) * n);
   return LLG_OK;
 }
 
@@ -508,6 +507,7 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
       ua.inv_beta = cf.inv_beta;
       ua.unew = U1 + size_t(j) * n4;
       ua.partial = c.partial;
+      ua.p = pslot;
       CHK(dcgs_coef(c, cf, pslot, &ua.gamma, st));
       CHK(fu->run(ua, W, c.dots2));
     } else {
@@ -516,25 +516,18 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
         dd.part = defer_part;
         dd.nb = defer_nb;
         dd.out = pslot;
-        dd.mirror = c.hmirror_dev + (pslot - c.dots);
       }
       CHK(dcgs_update(c, u0, U1, n4, cf, pslot, W, U1 + size_t(j) * n4, n4, c.dots2, st, &dd));
     }
-    // one round trip: pass-1 dots p and the pass-2 dots of u_{j+1}, which their
-    // reductions (on small grids the update pass itself) also wrote into the
-    // mapped host mirror.  On small grids the
-    // next step's operator (on u_{j+1}, which no host decision changes) is
-    // queued first, and the host waits only for this step's passes; when the
-    // cycle then ends, that work is discarded.
+    // one round trip: the pass-1 dots p and the pass-2 dots of u_{j+1}, which
+    // the latter's reduction posts to the host mirror (on small grids the
+    // update pass itself does).  On small grids the next step's operator (on
+    // u_{j+1}, which no host decision changes) is queued before the host
+    // waits; when the cycle then ends, that work is discarded.
     ahead = speculate && more;
     ready = fuse;
-    if (ahead) {
-      CHK(hipEventRecord(c.ev, st));
-      launch_op(j + 1, ((j + 1) & 1) ? c.dots_b : c.dots, ready);
-      CHK(hipEventSynchronize(c.ev));
-    } else {
-      CHK(hipStreamSynchronize(st));
-    }
+    if (ahead) launch_op(j + 1, ((j + 1) & 1) ? c.dots_b : c.dots, ready);
+    CHK(await_post(c, st));
     if (op_err != hipSuccess) {
       CHK(op_err);
     }
@@ -1106,18 +1099,20 @@ llg_status llg_ctx_create_cell(llg_ctx** out, int nx, int ny, int nz, double lx,
   if (hipMalloc(&c.spec, c.spec_bytes) != hipSuccess) return cleanup(LLG_ENOMEM, "spectral scratch allocation failed");
   if (hipMalloc(&c.partial, sizeof(double) * kRedBlocksMax * kMaxDots) != hipSuccess)
     return cleanup(LLG_ENOMEM, "reduction buffer allocation failed");
-  if (hipMalloc(&c.dots, sizeof(double) * kDotsSlots * kMaxDots) != hipSuccess)
+  if (hipMalloc(&c.dots, sizeof(double) * (kDotsSlots * kMaxDots + 1)) != hipSuccess)
     return cleanup(LLG_ENOMEM, "reduction buffer allocation failed");
+  c.post_count = reinterpret_cast<unsigned*>(c.dots + kDotsSlots * kMaxDots);
+  if (hipMemset(c.post_count, 0, sizeof(double)) != hipSuccess)
+    return cleanup(LLG_EHIP, "reduction buffer initialisation failed");
   c.dots2 = c.dots + kMaxDots;
   c.scal = c.dots + 2 * kMaxDots;
   c.dots_b = c.dots + 4 * kMaxDots;
-  if (hipEventCreateWithFlags(&c.ev, hipEventDisableTiming) != hipSuccess)
-    return cleanup(LLG_EHIP, "event creation failed");
   if (hipMalloc(&c.tri, sizeof(double) * (kDcgsMaxCols * kDcgsMaxCols + kDcgsMaxCols)) != hipSuccess)
     return cleanup(LLG_ENOMEM, "reduction buffer allocation failed");
-  if (hipHostMalloc(reinterpret_cast<void**>(&c.hmirror), sizeof(double) * kDotsSlots * kMaxDots,
+  if (hipHostMalloc(reinterpret_cast<void**>(&c.hmirror), sizeof(double) * (kDotsSlots * kMaxDots + 1),
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
     return cleanup(LLG_ENOMEM, "pinned host buffer allocation failed");
+  std::memset(c.hmirror, 0, sizeof(double) * (kDotsSlots * kMaxDots + 1));
   if (hipHostGetDevicePointer(reinterpret_cast<void**>(&c.hmirror_dev), c.hmirror, 0) != hipSuccess)
     return cleanup(LLG_EHIP, "device address of the pinned host buffer");
   if (hipHostMalloc(reinterpret_cast<void**>(&c.host), sizeof(double) * 4 * kMaxDots, hipHostMallocDefault) !=
@@ -1170,7 +1165,6 @@ llg_status llg_ctx_destroy(llg_ctx* ctx) {
   if (c.tri) (void)hipFree(c.tri);
   if (c.host) (void)hipHostFree(c.host);
   if (c.hmirror) (void)hipHostFree(c.hmirror);
-  if (c.ev) (void)hipEventDestroy(c.ev);
   if (c.prof) profiler_delete(c.prof);
   delete ctx;
   return LLG_OK;
@@ -1355,6 +1349,7 @@ llg_status llg::gmres_solve_work(llg_ctx* ctx, const llg_params* prm, const doub
   CHK_STATUS(ensure_device(c));
   SolveResult r;
   const llg_status s = solve(c, prm, m, b, x, *opts, w, r, as_stream(stream));
+  CHK(hipStreamSynchronize(as_stream(stream)));
   fill_stats(r, stats);
   if (stats) stats->ms = ms_since(t0);
   return s;
@@ -1376,7 +1371,9 @@ llg_status llg_energy(llg_ctx* ctx, const llg_params* prm, const double* m, doub
   CHK_STATUS(check_params(prm));
   CHK_STATUS(ensure_device(ctx->c));
   CHK_STATUS(check_aligned({m}));
-  return energy_of(ctx->c, prm, m, energy, as_stream(stream));
+  CHK_STATUS(energy_of(ctx->c, prm, m, energy, as_stream(stream)));
+  CHK(hipStreamSynchronize(as_stream(stream)));
+  return LLG_OK;
 }
 
 llg_status llg_step_euler(llg_ctx* ctx, const llg_params* prm, double* m, double* v_out, double* lam_out,
@@ -1653,6 +1650,7 @@ llg_status llg_step_midpoint_adjoint(llg_ctx* ctx, const llg_params* prm, const 
   CHK(adjoint_finish(c, nf, v, lam, w.x, w.l0, gbar, hbar_field, c.scal, st));
   double hs3[3];
   CHK_STATUS(fetch(c, c.scal, 3, st, hs3));
+  CHK(hipStreamSynchronize(st));
   if (hbar_uniform)
     for (int i = 0; i < 3; ++i) hbar_uniform[i] += hs3[i];
   (void)n4;

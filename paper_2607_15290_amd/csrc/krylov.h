@@ -20,6 +20,27 @@ struct DcgsCoef {
   int j;
 };
 
+// Results of a reduction for the host (device side of await_post): the values
+// go to their slots of the mapped host mirror, n_also further values are
+// copied there, and once every block's values are visible the last block sets
+// the host flag to seq.  The host polls the flag: no event or copy enters the
+// stream, and the wait ends as soon as the values arrive.
+struct Post {
+  double* mirror = nullptr;  // device address of the mirror slots of out
+  const double* also = nullptr;
+  double* also_mirror = nullptr;
+  int n_also = 0;
+  unsigned* count = nullptr;
+  unsigned long long* flag = nullptr;  // null: nothing to post
+  unsigned long long seq = 0;
+};
+// The next Post of a context for results at `out` (a slot of c.dots); empty
+// when out lies elsewhere.  also: n_also values of another slot.
+Post next_post(const Ctx& c, const double* out, const double* also = nullptr, int n_also = 0);
+// Waits until the latest Post has arrived; hipErrorUnknown when the stream
+// drains without it.
+hipError_t await_post(const Ctx& c, hipStream_t st);
+
 // Pass 1: out = [U_i.w (i <= j)].  j < kDcgsMaxCols.  w is float64, or the
 // float32 output of a float32 operator (its values convert exactly).
 hipError_t dcgs_dots(const Ctx& c, const double* u0, const double* U1, long long ld, int j, const double* w,
@@ -29,18 +50,18 @@ hipError_t dcgs_dots(const Ctx& c, const double* u0, const double* U1, long long
 // Pass-1 products left unreduced by the operator's last pass (small grids,
 // BasisDots::defer): nb block partials per value at part, value-major.  The
 // update pass reduces them (the same fixed order in every block), uses them,
-// and stores the reduced values at out (device) and mirror (host-mapped).
+// and stores the reduced values at out (device).
 struct DeferredDots {
   const double* part = nullptr;
   int nb = 0;
   double* out = nullptr;
-  double* mirror = nullptr;
 };
 
 // Pass 2 (p = pass-1 output on the device): with gamma = T_{j+1}^{-1} [b; e_j],
 // b = T_j^{-T} p_{<j}, e_j = (p_j - a.b) / beta_j (computed on the device),
 //   unew = (w - U gamma) / beta_j,   out = [U_i.unew (i <= j), unew.unew].
-// unew must not alias w or a basis column 0..j.
+// unew must not alias w or a basis column 0..j.  out and p (slots of c.dots)
+// are posted to the host.
 // With dp (dp->nb > 0) p is not read: the pass-1 products come from dp.
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const double* w, double* unew, long long n, double* out, hipStream_t st,
@@ -53,8 +74,9 @@ hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long lo
 // values) for a pass 2 run elsewhere (k_xfwd_upd).
 hipError_t dcgs_coef(const Ctx& c, const DcgsCoef& cf, const double* p, const double** gamma, hipStream_t st);
 
-// out[i] = sum (or max) of the nb value-major partials of value i, i < nv
-hipError_t reduce_partials(const Ctx& c, int nb, int nv, double* out, bool is_max, hipStream_t st);
+// out[i] = sum (or max) of the nb value-major partials of value i, i < nv;
+// with post, posted to the host when out is a slot of c.dots.
+hipError_t reduce_partials(const Ctx& c, int nb, int nv, double* out, bool is_max, hipStream_t st, bool post = true);
 // Blocks of a reducing streaming kernel over n elements: about four elements
 // per thread, at most kNodalBlocksMax; depends only on n (deterministic order).
 constexpr int kNodalBlocksMax = 16384;
@@ -63,8 +85,8 @@ inline int nodal_blocks(long long n) {
   if (g > kNodalBlocksMax) g = kNodalBlocksMax;
   return int(g < 1 ? 1 : g);
 }
-// out[i] = sum of the nb value-major partials of value i, i < nv (1024-thread reducer)
-hipError_t reduce_partials_n(const Ctx& c, int nb, int nv, double* out, hipStream_t st);
+// The same sums with an explicit Post (none by default).
+hipError_t reduce_partials_n(const Ctx& c, int nb, int nv, double* out, hipStream_t st, const Post& post = {});
 // Blocks of a delayed-CGS2 pass over n2 16-byte elements: one element per
 // thread of a 512-thread block (2 kRedThreads), at most kRedBlocksMax blocks
 // (grid-strided beyond); depends only on n2 (deterministic order).
@@ -73,7 +95,7 @@ inline int red_blocks(long long n2) {
   if (g > kRedBlocksMax) g = kRedBlocksMax;
   return int(g < 1 ? 1 : g);
 }
-// out[0] = sum of c.partial[0 .. nb) (the x-inverse residual partials)
+// out[0] = sum of c.partial[0 .. nb) (the x-inverse residual partials), posted
 hipError_t reduce_flat(const Ctx& c, int nb, double* out, hipStream_t st);
 // out[i] = V_i . w  (i < nv; V_i = V + i*ld)
 hipError_t cgs_dots(const Ctx& c, const double* V, long long ld, int nv, const double* w, long long n, double* out,

@@ -16,6 +16,7 @@
 #include <utility>
 
 #include "krylov.h"
+#include "post.h"
 #include "wave.h"
 
 namespace llg {
@@ -78,68 +79,31 @@ __device__ __forceinline__ void block_store(double (&acc)[MAXV], int nv, double*
   }
 }
 
-// out[i] = sum (or max) over blocks of partial[i * nb + b]; one block per value.
-template <bool MAX>
-__global__ __launch_bounds__(kRedThreads) void k_reduce(const double* __restrict__ partial, int nb,
-                                                       double* __restrict__ out) {
-  const int i = blockIdx.x;
-  double s = MAX ? -INFINITY : 0.0;
-  for (int b = threadIdx.x; b < nb; b += kRedThreads) {
-    const double v = partial[(long long)i * nb + b];
-    s = MAX ? fmax(s, v) : s + v;
-  }
-  __shared__ double sm[kRedThreads / 64];
-  s = MAX ? wave_max(s) : wave_sum(s);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = sm[0];
-    for (int w = 1; w < kRedThreads / 64; ++w) t = MAX ? fmax(t, sm[w]) : t + sm[w];
-    out[i] = t;
-  }
-}
-
-// out[0] = sum of partial[0 .. nb) (stride 1), fixed order
-__global__ __launch_bounds__(kRedThreads) void k_reduce_flat(const double* __restrict__ partial, int nb,
-                                                            double* __restrict__ out) {
-  double s = 0.0;
-  for (int b = threadIdx.x; b < nb; b += kRedThreads) s += partial[b];
-  __shared__ double sm[kRedThreads / 64];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = sm[0];
-    for (int w = 1; w < kRedThreads / 64; ++w) t += sm[w];
-    out[0] = t;
-  }
-}
-
-// out[i] = sum_b partial[i * nb + b]: value-major partials, one block of 1024
+// out[i] = sum (or max) over blocks of partial[i * nb + b]: one block of 1024
 // threads per value, four independent accumulators per thread (fixed order).
-__global__ __launch_bounds__(1024) void k_reduce_vmajor(const double* __restrict__ partial, int nb,
-                                                       double* __restrict__ out, double* __restrict__ hout) {
+template <bool MAX>
+__global__ __launch_bounds__(1024) void k_reduce(const double* __restrict__ partial, int nb,
+                                                double* __restrict__ out, Post ps) {
   const double* p = partial + (long long)blockIdx.x * nb;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  const double none = MAX ? -INFINITY : 0.0;
+  double s[4] = {none, none, none, none};
   int b = threadIdx.x;
   for (; b + 3 * 1024 < nb; b += 4 * 1024) {
-    s0 += p[b];
-    s1 += p[b + 1024];
-    s2 += p[b + 2048];
-    s3 += p[b + 3072];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = MAX ? fmax(s[k], p[b + k * 1024]) : s[k] + p[b + k * 1024];
   }
-  for (; b < nb; b += 1024) s0 += p[b];
-  double s = (s0 + s1) + (s2 + s3);
+  for (; b < nb; b += 1024) s[0] = MAX ? fmax(s[0], p[b]) : s[0] + p[b];
+  double t = MAX ? fmax(fmax(s[0], s[1]), fmax(s[2], s[3])) : (s[0] + s[1]) + (s[2] + s[3]);
   __shared__ double sm[1024 / 64];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = s;
+  t = MAX ? wave_max(t) : wave_sum(t);
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = t;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double t = sm[0];
-    for (int w = 1; w < 1024 / 64; ++w) t += sm[w];
+    t = sm[0];
+    for (int w = 1; w < 1024 / 64; ++w) t = MAX ? fmax(t, sm[w]) : t + sm[w];
     out[blockIdx.x] = t;
-    if (hout) hout[blockIdx.x] = t;
   }
+  post_value(ps, t);
 }
 
 // ---- CGS2 passes ----------------------------------------------------------
@@ -238,11 +202,11 @@ constexpr long long kDcgsSingleMaxN2 = 4 * kDcgsThreads;
 #define LLG_DCGS_UPDATE_LDS_F32W 40960
 #endif
 
-// With mirror (single-block launches only) the block's sums are the final
-// values and are also written to the host-mapped mirror.
+// With a Post (single-block launches only) the block's sums are the final
+// values and are posted to the host.
 template <int NV>
 __device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double* __restrict__ partial,
-                                                 double* __restrict__ mirror = nullptr) {
+                                                 const Post& ps = {}) {
   __shared__ double sm[kDcgsThreads / 64][NV];
   wave_sums_store<NV>(acc, sm[threadIdx.x >> 6]);
   __syncthreads();
@@ -251,8 +215,9 @@ __device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double
 #pragma unroll
     for (int k = 1; k < kDcgsThreads / 64; ++k) t += sm[k][threadIdx.x];
     partial[(long long)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    if (mirror) mirror[threadIdx.x] = t;
+    if (ps.flag) ps.mirror[threadIdx.x] = t;
   }
+  post_block(ps);
 }
 
 // Pass 1: out = [U_i.w (i <= J)], value-major partials.  W2: double2 or
@@ -338,7 +303,7 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
                                                             double2* __restrict__ unew, long long n2,
                                                             double* __restrict__ partial, DcgsCoef cf,
                                                             const double* __restrict__ p, double* __restrict__ minv,
-                                                            DeferredDots dp, double* __restrict__ mirror) {
+                                                            DeferredDots dp, Post ps) {
   double gm[J + 1];
   if constexpr (COEF) {
     __shared__ double gs[kDcgsMaxCols];
@@ -354,10 +319,7 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
         if (lane == 0) pr[q] = t;
       }
       __syncthreads();
-      if (blockIdx.x == 0 && threadIdx.x <= cf.j) {
-        dp.out[threadIdx.x] = pr[threadIdx.x];
-        dp.mirror[threadIdx.x] = pr[threadIdx.x];
-      }
+      if (blockIdx.x == 0 && threadIdx.x <= cf.j) dp.out[threadIdx.x] = pr[threadIdx.x];
       pp = pr;
     }
     dcgs_coef_block(cf, pp, minv, blockIdx.x == 0, gs);
@@ -388,7 +350,7 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
     for (int i = 0; i <= J; ++i) acc[i] = fma(q[i].x, un.x, fma(q[i].y, un.y, acc[i]));
     acc[J + 1] = fma(un.x, un.x, fma(un.y, un.y, acc[J + 1]));
   }
-  dcgs_block_store<J + 2>(acc, partial, mirror);
+  dcgs_block_store<J + 2>(acc, partial, ps);
 }
 
 // ---- simple vector kernels -------------------------------------------------
@@ -486,27 +448,53 @@ static inline unsigned grid_for(long long n) {
   return (unsigned)(g < 1 ? 1 : g);
 }
 
-hipError_t reduce_partials_n(const Ctx& c, int nb, int nv, double* out, hipStream_t st) {
+Post next_post(const Ctx& c, const double* out, const double* also, int n_also) {
+  Post ps;
+  if (out < c.dots || out >= c.dots + kDotsSlots * kMaxDots) return ps;
+  ps.mirror = c.hmirror_dev + (out - c.dots);
+  if (also) {
+    ps.also = also;
+    ps.also_mirror = c.hmirror_dev + (also - c.dots);
+    ps.n_also = n_also;
+  }
+  ps.count = c.post_count;
+  ps.flag = reinterpret_cast<unsigned long long*>(c.hmirror_dev + kDotsSlots * kMaxDots);
+  ps.seq = ++c.seq;
+  return ps;
+}
+
+hipError_t await_post(const Ctx& c, hipStream_t st) {
+  const unsigned long long* flag = reinterpret_cast<const unsigned long long*>(c.hmirror + kDotsSlots * kMaxDots);
+  const auto arrived = [&] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == c.seq; };
+  // the stream is asked now and then, so that a failed launch or a fault ends the wait
+  for (unsigned n = 1;; ++n) {
+    if (arrived()) return hipSuccess;
+    if (n % 65536 == 0) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess) return arrived() ? hipSuccess : hipErrorUnknown;
+      if (e != hipErrorNotReady) return e;
+    }
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+  }
+}
+
+hipError_t reduce_partials_n(const Ctx& c, int nb, int nv, double* out, hipStream_t st, const Post& post) {
   ProfScope ps(c.prof, st, KK_REDUCE, 8.0 * nb * nv);
-  // results landing in the Arnoldi slots are mirrored into host memory, so
-  // the host reads them after a stream synchronize without a copy
-  double* hout = (out >= c.dots && out < c.dots + kDotsSlots * kMaxDots) ? c.hmirror_dev + (out - c.dots) : nullptr;
-  hipLaunchKernelGGL(k_reduce_vmajor, dim3(nv), dim3(1024), 0, st, c.partial, nb, out, hout);
+  hipLaunchKernelGGL((k_reduce<false>), dim3(nv), dim3(1024), 0, st, c.partial, nb, out, post);
   return hipGetLastError();
 }
 
 hipError_t reduce_flat(const Ctx& c, int nb, double* out, hipStream_t st) {
-  ProfScope ps(c.prof, st, KK_REDUCE, 8.0 * nb);
-  hipLaunchKernelGGL(k_reduce_flat, dim3(1), dim3(kRedThreads), 0, st, c.partial, nb, out);
-  return hipGetLastError();
+  return reduce_partials_n(c, nb, 1, out, st, next_post(c, out));
 }
 
-hipError_t reduce_partials(const Ctx& c, int nb, int nv, double* out, bool is_max, hipStream_t st) {
+hipError_t reduce_partials(const Ctx& c, int nb, int nv, double* out, bool is_max, hipStream_t st, bool post) {
+  const Post po = post ? next_post(c, out) : Post{};
+  if (!is_max) return reduce_partials_n(c, nb, nv, out, st, po);
   ProfScope ps(c.prof, st, KK_REDUCE, 8.0 * nb * nv);
-  if (is_max)
-    hipLaunchKernelGGL((k_reduce<true>), dim3(nv), dim3(kRedThreads), 0, st, c.partial, nb, out);
-  else
-    hipLaunchKernelGGL((k_reduce<false>), dim3(nv), dim3(kRedThreads), 0, st, c.partial, nb, out);
+  hipLaunchKernelGGL((k_reduce<true>), dim3(nv), dim3(1024), 0, st, c.partial, nb, out, po);
   return hipGetLastError();
 }
 
@@ -523,7 +511,7 @@ hipError_t cgs_dots(const Ctx& c, const double* V, long long ld, int nv, const d
   else if (nv <= 32) mdot_t<32>(c, V, ld, nv, w, n, st);
   else mdot_t<64>(c, V, ld, nv, w, n, st);
   }
-  return reduce_partials(c, nodal_blocks(n), nv, out, false, st);
+  return reduce_partials(c, nodal_blocks(n), nv, out, false, st, false);
 }
 
 template <int MAXV>
@@ -541,7 +529,7 @@ hipError_t cgs_update_dots(const Ctx& c, const double* V, long long ld, int nv, 
   else if (nv <= 32) upd_t<32>(c, V, ld, nv, cf, w, n, st);
   else upd_t<64>(c, V, ld, nv, cf, w, n, st);
   }
-  return reduce_partials(c, nodal_blocks(n), nv, out, false, st);
+  return reduce_partials(c, nodal_blocks(n), nv, out, false, st, false);
 }
 
 template <int MAXV>
@@ -559,7 +547,7 @@ hipError_t cgs_update_norm(const Ctx& c, const double* V, long long ld, int nv, 
   else if (nv <= 32) updn_t<32>(c, V, ld, nv, cf, w, out_vec, n, st);
   else updn_t<64>(c, V, ld, nv, cf, w, out_vec, n, st);
   }
-  return reduce_partials(c, nodal_blocks(n), 1, out_nrm2, false, st);
+  return reduce_partials(c, nodal_blocks(n), 1, out_nrm2, false, st, false);
 }
 
 
@@ -578,19 +566,19 @@ static void dd_t(const Ctx& c, const double* u0, const double* U1, long long ld,
 template <int J, typename TW>
 static void du_t(const Ctx& c, const double* u0, const double* U1, long long ld, const double* gamma,
                  const DcgsCoef& cf, const double* p, const DeferredDots& dp, const TW* w, double* unew, long long n,
-                 double* part, double* mirror, hipStream_t st) {
+                 double* part, const Post& post, hipStream_t st) {
   constexpr unsigned lds = std::is_same<TW, float>::value ? LLG_DCGS_UPDATE_LDS_F32W : LLG_DCGS_UPDATE_LDS;
-  const dim3 grid(mirror ? 1 : red_blocks(n / 2)), block(kDcgsThreads);
+  const dim3 grid(post.flag ? 1 : red_blocks(n / 2)), block(kDcgsThreads);
   const double2* a0 = reinterpret_cast<const double2*>(u0);
   const double2* a1 = reinterpret_cast<const double2*>(U1);
   const pair_of<TW>* wp = reinterpret_cast<const pair_of<TW>*>(w);
   double2* un = reinterpret_cast<double2*>(unew);
   if (gamma)
     hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>, false>), grid, block, lds, st, a0, a1, ld / 2, gamma,
-                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, mirror);
+                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, post);
   else
     hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>, true>), grid, block, lds, st, a0, a1, ld / 2, nullptr,
-                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, mirror);
+                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, post);
 }
 
 // Runtime J -> template instantiation J = 0..kDcgsMaxCols - 1.
@@ -649,7 +637,7 @@ static hipError_t dcgs_update_t(const Ctx& c, const double* u0, const double* U1
                                 hipStream_t st, const DeferredDots* dpp) {
   if (cf.j < 0 || cf.j >= kDcgsMaxCols) return hipErrorInvalidValue;
   const DeferredDots dp = dpp ? *dpp : DeferredDots{};
-  if (dp.nb > 0 && (!dp.part || !dp.out || !dp.mirror)) return hipErrorInvalidValue;
+  if (dp.nb > 0 && (!dp.part || !dp.out)) return hipErrorInvalidValue;
   // small grids (and deferred pass-1 products): the update pass forms gamma
   // itself (one launch fewer)
   const double* gamma = nullptr;
@@ -657,18 +645,18 @@ static hipError_t dcgs_update_t(const Ctx& c, const double* u0, const double* U1
     hipError_t e = dcgs_coef(c, cf, p, &gamma, st);
     if (e != hipSuccess) return e;
   }
-  // Vectors of at most kDcgsSingleMaxN2 pairs: one block (grid-strided)
-  // whose sums are the final products, written to out and, for a mirrored
-  // slot, to its host mirror: no reduction launch.
-  const bool single = n / 2 <= kDcgsSingleMaxN2 && out >= c.dots && out < c.dots + kDotsSlots * kMaxDots;
+  // Vectors of at most kDcgsSingleMaxN2 pairs: one block (grid-strided) whose
+  // sums are the final products: no reduction launch.
+  const bool single = n / 2 <= kDcgsSingleMaxN2;
+  const Post post = next_post(c, out, p, cf.j + 1);
   {
     // j + 1 directions read, w read, u_new written
     ProfScope ps(c.prof, st, KK_CGS_UPDATE_DOTS, double(n) * (8.0 * (cf.j + 2) + sizeof(TW)));
     JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, single ? out : c.partial,
-                         single ? c.hmirror_dev + (out - c.dots) : nullptr, st);
+                         single ? post : Post{}, st);
   }
   if (single) return hipGetLastError();
-  return reduce_partials_n(c, red_blocks(n / 2), cf.j + 2, out, st);
+  return reduce_partials_n(c, red_blocks(n / 2), cf.j + 2, out, st, post);
 }
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const double* w, double* unew, long long n, double* out, hipStream_t st,

@@ -74,9 +74,11 @@ struct Ctx {
   double* scal = nullptr;
   double* dots_b = nullptr;
   double* host = nullptr;     // pinned host mirror (4 * kMaxDots doubles)
-  double* hmirror = nullptr;      // pinned, device-mapped host copy of the reduced values (same layout)
+  double* hmirror = nullptr;      // pinned, device-mapped host copy of the reduced values (same layout),
+                                  // followed by the flag of the latest Post (krylov.h)
   double* hmirror_dev = nullptr;  // its device address
-  hipEvent_t ev = nullptr;    // marks the end of an Arnoldi step's second pass
+  unsigned* post_count = nullptr; // blocks of a Post that have arrived (device, 0 between Posts)
+  mutable unsigned long long seq = 0;  // number of the latest Post
   double* tri = nullptr;      // delayed-CGS2 T^{-1} (kDcgsMaxCols^2, column-major) + kDcgsMaxCols coefficients
 };
 

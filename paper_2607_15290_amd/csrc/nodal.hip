@@ -11,6 +11,7 @@
 #include <cmath>
 
 #include "krylov.h"
+#include "post.h"
 #include "wave.h"
 
 namespace llg {
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(kRedThreads) void k_adjoint_finish(NodalArgs na, co
 }
 
 __global__ __launch_bounds__(kRedThreads) void k_reduce_min_max(const double* __restrict__ partial, int nb,
-                                                               double* __restrict__ out) {
+                                                               double* __restrict__ out, Post ps) {
   double mn[1] = {INFINITY}, mx[1] = {-INFINITY};
   for (int b = threadIdx.x; b < nb; b += kRedThreads) {
     mn[0] = fmin(mn[0], partial[b]);
@@ -339,7 +340,12 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_min_max(const double* __
     }
     out[0] = x;
     out[1] = y;
+    if (ps.flag) {
+      ps.mirror[0] = x;
+      ps.mirror[1] = y;
+    }
   }
+  post_block(ps);
 }
 
 // ---- launchers --------------------------------------------------------------
@@ -357,7 +363,8 @@ hipError_t m_check(const Ctx& c, const double* m, double* out, hipStream_t st) {
   ProfScope ps(c.prof, st, KK_NODAL, 24.0 * c.ng);
   const int nb = nodal_blocks(c.ng);
   hipLaunchKernelGGL(k_m_check, dim3(nb), dim3(kRedThreads), 0, st, m, c.ng, c.partial);
-  hipLaunchKernelGGL((k_reduce_min_max), dim3(1), dim3(kRedThreads), 0, st, c.partial, nb, out);
+  hipLaunchKernelGGL((k_reduce_min_max), dim3(1), dim3(kRedThreads), 0, st, c.partial, nb, out,
+                     next_post(c, out));
   e_ = hipGetLastError();
   }
   return e_;

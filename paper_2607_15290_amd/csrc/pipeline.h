@@ -212,6 +212,7 @@ struct UpdFirst {
   long long ld = 0;
   int j = 0;
   const double* gamma = nullptr;  // j + 1 coefficients (device)
+  const double* p = nullptr;      // pass-1 products (posted to the host with the new ones)
   double inv_beta = 0;
   double* unew = nullptr;         // must not alias w or a basis column 0..j
   double* partial = nullptr;

@@ -60,7 +60,7 @@ hipError_t upd_nh(const Ctx& c, const NodalArgs& na, const UpdFirst& ua, const W
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return reduce_partials_n(c, int(grid), ua.j + 2, out, st);
+  return reduce_partials_n(c, int(grid), ua.j + 2, out, st, next_post(c, out, ua.p, ua.j + 1));
 }
 
 template <typename T, typename W, int NH>
