@@ -447,6 +447,7 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
   const bool defer = speculate && op_dots && !(LLG_FUSE_UPDATE && fu && fu->ok(0));
   double* const defer_part = c.partial + size_t(kRedBlocksMax) * kMaxDots / 2;
   int defer_nb = 0;
+  RideReduce ride;  // pass-2 reduction of the latest step, carried by the next operator
   // Operator of step jj on u_jj into W, its pass-1 products into pslot.
   hipError_t op_err = hipSuccess;
   auto launch_op = [&](int jj, double* pslot, bool spec_ready) {
@@ -459,6 +460,7 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
         bq.defer = defer_part;
         bq.defer_nb = &defer_nb;
       }
+      if (ride.nv > 0) bq.ride = &ride;
       e = op(jj, ujj, W, &bq, spec_ready);
     } else {
       e = op(jj, ujj, W, nullptr, spec_ready);
@@ -517,7 +519,9 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
         dd.nb = defer_nb;
         dd.out = pslot;
       }
-      CHK(dcgs_update(c, u0, U1, n4, cf, pslot, W, U1 + size_t(j) * n4, n4, c.dots2, st, &dd));
+      ride = RideReduce{};
+      CHK(dcgs_update(c, u0, U1, n4, cf, pslot, W, U1 + size_t(j) * n4, n4, c.dots2, st, &dd,
+                      defer && more ? &ride : nullptr));
     }
     // one round trip: the pass-1 dots p and the pass-2 dots of u_{j+1}, which
     // the latter's reduction posts to the host mirror (on small grids the
@@ -527,10 +531,8 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
     ahead = speculate && more;
     ready = fuse;
     if (ahead) launch_op(j + 1, ((j + 1) & 1) ? c.dots_b : c.dots, ready);
+    CHK(op_err);
     CHK(await_post(c, st));
-    if (op_err != hipSuccess) {
-      CHK(op_err);
-    }
     std::memcpy(vals.data(), c.hmirror + (pslot - c.dots), sizeof(double) * kMaxDots);
     std::memcpy(vals.data() + kMaxDots, c.hmirror + kMaxDots, sizeof(double) * kMaxDots);
     const double* p = vals.data();

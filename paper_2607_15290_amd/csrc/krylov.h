@@ -20,20 +20,6 @@ struct DcgsCoef {
   int j;
 };
 
-// Results of a reduction for the host (device side of await_post): the values
-// go to their slots of the mapped host mirror, n_also further values are
-// copied there, and once every block's values are visible the last block sets
-// the host flag to seq.  The host polls the flag: no event or copy enters the
-// stream, and the wait ends as soon as the values arrive.
-struct Post {
-  double* mirror = nullptr;  // device address of the mirror slots of out
-  const double* also = nullptr;
-  double* also_mirror = nullptr;
-  int n_also = 0;
-  unsigned* count = nullptr;
-  unsigned long long* flag = nullptr;  // null: nothing to post
-  unsigned long long seq = 0;
-};
 // The next Post of a context for results at `out` (a slot of c.dots); empty
 // when out lies elsewhere.  also: n_also values of another slot.
 Post next_post(const Ctx& c, const double* out, const double* also = nullptr, int n_also = 0);
@@ -62,13 +48,15 @@ struct DeferredDots {
 //   unew = (w - U gamma) / beta_j,   out = [U_i.unew (i <= j), unew.unew].
 // unew must not alias w or a basis column 0..j.  out and p (slots of c.dots)
 // are posted to the host.
+// With ride (filled when the pass has at most kRideMaxBlocks blocks) the
+// reduction into out is left to the next operator's x-forward pass.
 // With dp (dp->nb > 0) p is not read: the pass-1 products come from dp.
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const double* w, double* unew, long long n, double* out, hipStream_t st,
-                       const DeferredDots* dp = nullptr);
+                       const DeferredDots* dp = nullptr, RideReduce* ride = nullptr);
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const float* w, double* unew, long long n, double* out, hipStream_t st,
-                       const DeferredDots* dp = nullptr);
+                       const DeferredDots* dp = nullptr, RideReduce* ride = nullptr);
 
 // The coefficient step of pass 2 alone (k_dcgs_coef): gamma (device, j + 1
 // values) for a pass 2 run elsewhere (k_xfwd_upd).

@@ -27,25 +27,17 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// 16-byte load / store of a Krylov vector, with the non-temporal hint (NT)
-// where the vectors are streamed (hundreds of MB each, never reused from cache
-// before eviction) and without it on grids whose basis stays in the caches.
-template <bool NT = true>
+// Non-temporal 16-byte load / store: the Krylov vectors (hundreds of MB each)
+// are streamed once per pass and never reused from cache before eviction.
 __device__ __forceinline__ double2 ldnt(const double2* p) {
-  if constexpr (!NT) return *p;
   double2 v;
   v.x = __builtin_nontemporal_load(&p->x);
   v.y = __builtin_nontemporal_load(&p->y);
   return v;
 }
-template <bool NT = true>
 __device__ __forceinline__ void stnt(double2* p, double2 v) {
-  if constexpr (!NT) {
-    *p = v;
-  } else {
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-  }
+  __builtin_nontemporal_store(v.x, &p->x);
+  __builtin_nontemporal_store(v.y, &p->y);
 }
 // The operator output w of an Arnoldi step, as a pair of float64 values: a
 // float64 vector, or the float32 output of the precision form's operators
@@ -186,8 +178,6 @@ __global__ __launch_bounds__(kRedThreads) void k_update_norm(const double* __res
 // elements' loads per thread, whose extra streams in flight lower the DRAM
 // efficiency).
 constexpr int kDcgsThreads = 512;
-// The update pass of vectors of at most this many 16-byte pairs runs as one block.
-constexpr long long kDcgsSingleMaxN2 = 4 * kDcgsThreads;
 // Unused dynamic LDS of the update pass caps the blocks per CU.  With a
 // float64 operator output w it caps the pass at two 512-thread blocks per CU
 // (16 waves): fewer concurrent vector streams keep the DRAM pages of the
@@ -202,11 +192,8 @@ constexpr long long kDcgsSingleMaxN2 = 4 * kDcgsThreads;
 #define LLG_DCGS_UPDATE_LDS_F32W 40960
 #endif
 
-// With a Post (single-block launches only) the block's sums are the final
-// values and are posted to the host.
 template <int NV>
-__device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double* __restrict__ partial,
-                                                 const Post& ps = {}) {
+__device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double* __restrict__ partial) {
   __shared__ double sm[kDcgsThreads / 64][NV];
   wave_sums_store<NV>(acc, sm[threadIdx.x >> 6]);
   __syncthreads();
@@ -215,9 +202,7 @@ __device__ __forceinline__ void dcgs_block_store(const double (&acc)[NV], double
 #pragma unroll
     for (int k = 1; k < kDcgsThreads / 64; ++k) t += sm[k][threadIdx.x];
     partial[(long long)threadIdx.x * gridDim.x + blockIdx.x] = t;
-    if (ps.flag) ps.mirror[threadIdx.x] = t;
   }
-  post_block(ps);
 }
 
 // Pass 1: out = [U_i.w (i <= J)], value-major partials.  W2: double2 or
@@ -248,87 +233,84 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_dots(const double2* __res
 // column j in cf):
 //   b = Q_j^T w = Minv_j^T p_{<j},   e_j = q_j.w = (p_j - a.b) / beta_j,
 //   Q_{j+1} [b; e_j] = U_{j+1} gamma,   gamma = Minv_{j+1} [b; e_j].
-// The coefficient step inside a block: columns 0..j of Minv (column j from
-// cf) and p are staged in LDS with coalesced loads by the whole block, then
-// the first wavefront runs the two short triangular products from LDS (from
-// global memory each term of those loops would wait out a cache latency).
-// gs (LDS) receives gamma; with store, the block keeps column j of Minv for
-// the later steps.  Every thread of the block calls it.
-__device__ __forceinline__ void dcgs_coef_block(const DcgsCoef& cf, const double* __restrict__ p,
-                                                double* __restrict__ minv, bool store, double* gs) {
-  __shared__ double ms[kDcgsMaxCols * kDcgsMaxCols];  // column-major, columns 0..j
-  __shared__ double ps[kDcgsMaxCols];
-  __shared__ double v[64];
-  const int l = threadIdx.x, j = cf.j;
-  for (int t = l; t < (j + 1) * kDcgsMaxCols; t += blockDim.x)
-    ms[t] = t < j * kDcgsMaxCols ? minv[t] : cf.minv[t - j * kDcgsMaxCols];
-  if (l <= j) ps[l] = p[l];
+// The coefficient step inside a block of NT threads: columns 0..j of Minv
+// (column j from cf) are staged in LDS with coalesced loads, ps (LDS) holds
+// p.  The two triangular products take 16 lanes per row (two terms each,
+// then a sum over the 16-lane row): a lane that walked a whole row spent a
+// cache or LDS latency per term, 3-4 us of a small grid's update pass.  gs
+// (LDS) receives gamma; with store, the block keeps column j of Minv for the
+// later steps.  Every thread of the block calls it (ps stored before).
+__device__ __forceinline__ double row16_sum(double v) {
+  v += dpp_get<kDppBit3>(v);
+  v += dpp_get<kDppBit2>(v);
+  v += dpp_get<kDppBit1>(v);
+  v += dpp_get<kDppBit0>(v);
+  return v;
+}
+template <int NT>
+__device__ __forceinline__ void dcgs_coef_block(const DcgsCoef& cf, const double* ps, double* __restrict__ minv,
+                                                bool store, double* gs) {
+  constexpr int S = kDcgsMaxCols + 1;           // LDS column stride
+  __shared__ double ms[kDcgsMaxCols * S];       // column-major, columns 0..j
+  __shared__ double v[kDcgsMaxCols], as[kDcgsMaxCols];
+  static_assert(NT % 64 == 0 && kDcgsMaxCols == 32, "16 lanes per row, 32 rows");
+  const int t = threadIdx.x, j = cf.j;
+  for (int k = t; k < (j + 1) * kDcgsMaxCols; k += NT)
+    ms[k / kDcgsMaxCols * S + k % kDcgsMaxCols] = k < j * kDcgsMaxCols ? minv[k] : cf.minv[k - j * kDcgsMaxCols];
+  if (t < kDcgsMaxCols) as[t] = t < j ? cf.a[t] : 0.0;
   __syncthreads();
-  if (l < 64) {
+  const int part = t % 16;
+#pragma unroll
+  for (int l = t / 16; l < kDcgsMaxCols; l += NT / 16) {
     double b = 0.0;
-    if (l < j)
-      for (int k = 0; k <= l; ++k) b = fma(ms[l * kDcgsMaxCols + k], ps[k], b);
-    const double ab = wave_sum(l < j ? cf.a[l] * b : 0.0);
-    const double e = (ps[j] - ab) * cf.inv_beta;
-    v[l] = l < j ? b : (l == j ? e : 0.0);
+    if (l < j) {
+      if (part <= l) b = ms[l * S + part] * ps[part];
+      if (part + 16 <= l) b = fma(ms[l * S + part + 16], ps[part + 16], b);
+    }
+    b = row16_sum(b);
+    if (part == 0) v[l] = b;
   }
   __syncthreads();
-  if (l <= j) {
+  const int lane = t & 63;
+  const double ab = wave_sum(lane < j ? as[lane] * v[lane] : 0.0);
+  const double e = (ps[j] - ab) * cf.inv_beta;
+#pragma unroll
+  for (int l = t / 16; l < kDcgsMaxCols; l += NT / 16) {
     double g = 0.0;
-    for (int k = l; k <= j; ++k) g = fma(ms[k * kDcgsMaxCols + l], v[k], g);
-    gs[l] = g;
-    if (store) minv[j * kDcgsMaxCols + l] = cf.minv[l];
+    if (part >= l && part <= j) g = ms[part * S + l] * (part == j ? e : v[part]);
+    if (part + 16 >= l && part + 16 <= j)
+      g = fma(ms[(part + 16) * S + l], part + 16 == j ? e : v[part + 16], g);
+    g = row16_sum(g);
+    if (part == 0 && l <= j) {
+      gs[l] = g;
+      if (store) minv[j * kDcgsMaxCols + l] = cf.minv[l];
+    }
   }
   __syncthreads();
 }
 
-// Pass 2's coefficients as a kernel of their own (one block of one wavefront).
-__global__ __launch_bounds__(64) void k_dcgs_coef(DcgsCoef cf, const double* __restrict__ p,
-                                                  double* __restrict__ minv, double* __restrict__ gamma) {
-  __shared__ double gs[kDcgsMaxCols];
-  dcgs_coef_block(cf, p, minv, true, gs);
+// Pass 2's coefficients as a kernel of their own (one block).
+constexpr int kCoefThreads = 512;
+__global__ __launch_bounds__(kCoefThreads) void k_dcgs_coef(DcgsCoef cf, const double* __restrict__ p,
+                                                            double* __restrict__ minv, double* __restrict__ gamma) {
+  __shared__ double gs[kDcgsMaxCols], ps[kDcgsMaxCols];
+  if (threadIdx.x <= cf.j) ps[threadIdx.x] = p[threadIdx.x];
+  dcgs_coef_block<kCoefThreads>(cf, ps, minv, true, gs);
   if (threadIdx.x <= cf.j) gamma[threadIdx.x] = gs[threadIdx.x];
 }
 
 // Pass 2: unew = (w - U gamma) / beta_j, and, for the next step,
-// out = [U_i.unew (i <= J), unew.unew], value-major partials.  With COEF the
-// pass forms gamma itself (dcgs_coef_block, from cf and the pass-1 products
-// p) instead of reading the coefficient kernel's output: on small grids that
-// saves a launch per step, where launches, not bytes, set the time.
-template <int J, typename W2, bool COEF>
+// out = [U_i.unew (i <= J), unew.unew], value-major partials.
+template <int J, typename W2>
 __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __restrict__ u0,
                                                             const double2* __restrict__ U1, long long ld2,
                                                             const double* __restrict__ gamma, double inv_beta,
                                                             const W2* __restrict__ w,
                                                             double2* __restrict__ unew, long long n2,
-                                                            double* __restrict__ partial, DcgsCoef cf,
-                                                            const double* __restrict__ p, double* __restrict__ minv,
-                                                            DeferredDots dp, Post ps) {
+                                                            double* __restrict__ partial) {
   double gm[J + 1];
-  if constexpr (COEF) {
-    __shared__ double gs[kDcgsMaxCols];
-    __shared__ double pr[kDcgsMaxCols];
-    const double* pp = p;
-    if (dp.nb > 0) {
-      // reduce the deferred pass-1 partials: value q by wavefront q mod 8
-      const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-      for (int q = wv; q <= cf.j; q += kDcgsThreads / 64) {
-        double t = 0.0;
-        for (int b = lane; b < dp.nb; b += 64) t += dp.part[(long long)q * dp.nb + b];
-        t = wave_sum(t);
-        if (lane == 0) pr[q] = t;
-      }
-      __syncthreads();
-      if (blockIdx.x == 0 && threadIdx.x <= cf.j) dp.out[threadIdx.x] = pr[threadIdx.x];
-      pp = pr;
-    }
-    dcgs_coef_block(cf, pp, minv, blockIdx.x == 0, gs);
 #pragma unroll
-    for (int i = 0; i <= J; ++i) gm[i] = gs[i];
-  } else {
-#pragma unroll
-    for (int i = 0; i <= J; ++i) gm[i] = gamma[i];
-  }
+  for (int i = 0; i <= J; ++i) gm[i] = gamma[i];
   double acc[J + 2];
 #pragma unroll
   for (int i = 0; i < J + 2; ++i) acc[i] = 0.0;
@@ -336,21 +318,68 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n2; e += stride) {
     double2 se = ldw(w + e);
     double2 q[J + 1];
-    q[0] = ldnt<!COEF>(u0 + e);
+    q[0] = ldnt(u0 + e);
 #pragma unroll
-    for (int i = 1; i <= J; ++i) q[i] = ldnt<!COEF>(U1 + (i - 1) * ld2 + e);
+    for (int i = 1; i <= J; ++i) q[i] = ldnt(U1 + (i - 1) * ld2 + e);
 #pragma unroll
     for (int i = 0; i <= J; ++i) {
       se.x = fma(-gm[i], q[i].x, se.x);
       se.y = fma(-gm[i], q[i].y, se.y);
     }
     const double2 un{se.x * inv_beta, se.y * inv_beta};
-    stnt<!COEF>(unew + e, un);
+    stnt(unew + e, un);
 #pragma unroll
     for (int i = 0; i <= J; ++i) acc[i] = fma(q[i].x, un.x, fma(q[i].y, un.y, acc[i]));
     acc[J + 1] = fma(un.x, un.x, fma(un.y, un.y, acc[J + 1]));
   }
-  dcgs_block_store<J + 2>(acc, partial, ps);
+  dcgs_block_store<J + 2>(acc, partial);
+}
+
+// Pass 2 of small grids, where latencies and launches, not bytes, set the
+// time: one 16-byte pair per thread, whose loads are issued first; while they
+// are in flight every block reduces the operator's unreduced pass-1 products
+// (dp, or reads the reduced p) and forms gamma itself.  No non-temporal hints:
+// the basis stays in the caches.
+template <int J, typename W2>
+__global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update_small(const double2* __restrict__ u0,
+                                                                  const double2* __restrict__ U1, long long ld2,
+                                                                  const W2* __restrict__ w,
+                                                                  double2* __restrict__ unew, long long n2,
+                                                                  double* __restrict__ partial, DcgsCoef cf,
+                                                                  const double* __restrict__ p,
+                                                                  double* __restrict__ minv, DeferredDots dp) {
+  __shared__ double gs[kDcgsMaxCols], pr[kDcgsMaxCols];
+  const long long e0 = (long long)blockIdx.x * kDcgsThreads + threadIdx.x;
+  const bool live = e0 < n2;
+  const long long e = live ? e0 : n2 - 1;
+  const W2 wv = w[e];
+  double2 q[J + 1];
+  q[0] = u0[e];
+#pragma unroll
+  for (int i = 1; i <= J; ++i) q[i] = U1[(i - 1) * ld2 + e];
+  if (dp.nb > 0) {
+    rows_sum<kDcgsThreads / 64>(dp.part, dp.nb, cf.j + 1, [&](int k, double s) {
+      pr[k] = s;
+      if (blockIdx.x == 0) dp.out[k] = s;
+    });
+  } else if (threadIdx.x <= cf.j) {
+    pr[threadIdx.x] = p[threadIdx.x];
+  }
+  dcgs_coef_block<kDcgsThreads>(cf, pr, minv, blockIdx.x == 0, gs);
+  double2 se{double(wv.x), double(wv.y)};
+#pragma unroll
+  for (int i = 0; i <= J; ++i) {
+    const double g = gs[i];
+    se.x = fma(-g, q[i].x, se.x);
+    se.y = fma(-g, q[i].y, se.y);
+  }
+  const double2 un{live ? se.x * cf.inv_beta : 0.0, live ? se.y * cf.inv_beta : 0.0};
+  if (live) unew[e] = un;
+  double acc[J + 2];
+#pragma unroll
+  for (int i = 0; i <= J; ++i) acc[i] = fma(q[i].x, un.x, q[i].y * un.y);
+  acc[J + 1] = fma(un.x, un.x, un.y * un.y);
+  dcgs_block_store<J + 2>(acc, partial);
 }
 
 // ---- simple vector kernels -------------------------------------------------
@@ -566,19 +595,19 @@ static void dd_t(const Ctx& c, const double* u0, const double* U1, long long ld,
 template <int J, typename TW>
 static void du_t(const Ctx& c, const double* u0, const double* U1, long long ld, const double* gamma,
                  const DcgsCoef& cf, const double* p, const DeferredDots& dp, const TW* w, double* unew, long long n,
-                 double* part, const Post& post, hipStream_t st) {
+                 hipStream_t st) {
   constexpr unsigned lds = std::is_same<TW, float>::value ? LLG_DCGS_UPDATE_LDS_F32W : LLG_DCGS_UPDATE_LDS;
-  const dim3 grid(post.flag ? 1 : red_blocks(n / 2)), block(kDcgsThreads);
+  const dim3 grid(red_blocks(n / 2)), block(kDcgsThreads);
   const double2* a0 = reinterpret_cast<const double2*>(u0);
   const double2* a1 = reinterpret_cast<const double2*>(U1);
   const pair_of<TW>* wp = reinterpret_cast<const pair_of<TW>*>(w);
   double2* un = reinterpret_cast<double2*>(unew);
   if (gamma)
-    hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>, false>), grid, block, lds, st, a0, a1, ld / 2, gamma,
-                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, post);
+    hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>>), grid, block, lds, st, a0, a1, ld / 2, gamma, cf.inv_beta, wp,
+                       un, n / 2, c.partial);
   else
-    hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>, true>), grid, block, lds, st, a0, a1, ld / 2, nullptr,
-                       cf.inv_beta, wp, un, n / 2, part, cf, p, c.tri, dp, post);
+    hipLaunchKernelGGL((k_dcgs_update_small<J, pair_of<TW>>), grid, block, 0, st, a0, a1, ld / 2, wp, un, n / 2,
+                       c.partial, cf, p, c.tri, dp);
 }
 
 // Runtime J -> template instantiation J = 0..kDcgsMaxCols - 1.
@@ -625,7 +654,7 @@ hipError_t dcgs_coef(const Ctx& c, const DcgsCoef& cf, const double* p, const do
   double* g = c.tri + kDcgsMaxCols * kDcgsMaxCols;
   {
     ProfScope ps(c.prof, st, KK_REDUCE, 8.0 * (cf.j + 1) * (cf.j + 3));
-    hipLaunchKernelGGL(k_dcgs_coef, dim3(1), dim3(64), 0, st, cf, p, c.tri, g);
+    hipLaunchKernelGGL(k_dcgs_coef, dim3(1), dim3(kCoefThreads), 0, st, cf, p, c.tri, g);
   }
   *gamma = g;
   return hipGetLastError();
@@ -634,39 +663,44 @@ hipError_t dcgs_coef(const Ctx& c, const DcgsCoef& cf, const double* p, const do
 template <typename TW>
 static hipError_t dcgs_update_t(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                                 const double* p, const TW* w, double* unew, long long n, double* out,
-                                hipStream_t st, const DeferredDots* dpp) {
+                                hipStream_t st, const DeferredDots* dpp, RideReduce* ride) {
   if (cf.j < 0 || cf.j >= kDcgsMaxCols) return hipErrorInvalidValue;
   const DeferredDots dp = dpp ? *dpp : DeferredDots{};
   if (dp.nb > 0 && (!dp.part || !dp.out)) return hipErrorInvalidValue;
   // small grids (and deferred pass-1 products): the update pass forms gamma
-  // itself (one launch fewer)
+  // itself (one launch fewer); it takes one pair per thread
   const double* gamma = nullptr;
   if (c.ng > kSpeculateMaxNodes && dp.nb == 0) {
     hipError_t e = dcgs_coef(c, cf, p, &gamma, st);
     if (e != hipSuccess) return e;
   }
-  // Vectors of at most kDcgsSingleMaxN2 pairs: one block (grid-strided) whose
-  // sums are the final products: no reduction launch.
-  const bool single = n / 2 <= kDcgsSingleMaxN2;
-  const Post post = next_post(c, out, p, cf.j + 1);
+  const int nb = red_blocks(n / 2);
+  if (!gamma && (long long)nb * kDcgsThreads < n / 2) return hipErrorInvalidValue;
   {
     // j + 1 directions read, w read, u_new written
     ProfScope ps(c.prof, st, KK_CGS_UPDATE_DOTS, double(n) * (8.0 * (cf.j + 2) + sizeof(TW)));
-    JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, single ? out : c.partial,
-                         single ? post : Post{}, st);
+    JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, st);
   }
-  if (single) return hipGetLastError();
-  return reduce_partials_n(c, red_blocks(n / 2), cf.j + 2, out, st, post);
+  const Post post = next_post(c, out, p, cf.j + 1);
+  if (ride && nb <= kRideMaxBlocks) {
+    ride->part = c.partial;
+    ride->nb = nb;
+    ride->nv = cf.j + 2;
+    ride->out = out;
+    ride->post = post;
+    return hipGetLastError();
+  }
+  return reduce_partials_n(c, nb, cf.j + 2, out, st, post);
 }
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const double* w, double* unew, long long n, double* out, hipStream_t st,
-                       const DeferredDots* dp) {
-  return dcgs_update_t(c, u0, U1, ld, cf, p, w, unew, n, out, st, dp);
+                       const DeferredDots* dp, RideReduce* ride) {
+  return dcgs_update_t(c, u0, U1, ld, cf, p, w, unew, n, out, st, dp, ride);
 }
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const float* w, double* unew, long long n, double* out, hipStream_t st,
-                       const DeferredDots* dp) {
-  return dcgs_update_t(c, u0, U1, ld, cf, p, w, unew, n, out, st, dp);
+                       const DeferredDots* dp, RideReduce* ride) {
+  return dcgs_update_t(c, u0, U1, ld, cf, p, w, unew, n, out, st, dp, ride);
 }
 
 hipError_t scale_invnorm(const Ctx& c, double* y, const double* x, const double* nrm2, long long n, hipStream_t st) {

@@ -175,6 +175,31 @@ struct PipeIO {
   T* out_f = nullptr;
 };
 
+// Results of a reduction for the host (device side of await_post): the values
+// go to their slots of the mapped host mirror, n_also further values are
+// copied there, and once every block's values are visible the last block sets
+// the host flag to seq.  The host polls the flag: no event or copy enters the
+// stream, and the wait ends as soon as the values arrive.
+struct Post {
+  double* mirror = nullptr;  // device address of the mirror slots of out
+  const double* also = nullptr;
+  double* also_mirror = nullptr;
+  int n_also = 0;
+  unsigned* count = nullptr;
+  unsigned long long* flag = nullptr;  // null: nothing to post
+  unsigned long long seq = 0;
+};
+// A reduction (nv rows of nb block partials, value-major, into out and the
+// Post) that rides in the next x-forward pass as its block 0: on small grids
+// it takes the place of a launch of its own between two passes.
+struct RideReduce {
+  const double* part = nullptr;
+  int nb = 0, nv = 0;  // nv = 0: nothing rides
+  double* out = nullptr;
+  Post post;
+};
+constexpr int kRideMaxBlocks = 1024;
+
 // Arnoldi inner products taken by an x-inverse pass on its own output (the
 // precision form's matvec): with basis directions u_0 at u0 and u_i at
 // U1 + (i - 1) ld (1 <= i < nv), each block stores the partial sums of
@@ -187,16 +212,19 @@ struct BasisDots {
   int nv = 0;
   double* partial = nullptr;
   double* out = nullptr;  // when set, the reduced products go here instead of the caller's default
-  // Deferred reduction (small grids): when defer is set and the pass has at
-  // most kDeferMaxBlocks blocks, it leaves its block partials at defer
+  // Deferred reduction (small grids): when defer is set and the pass has few
+  // enough blocks (kDeferMaxSums), it leaves its block partials at defer
   // (value-major) instead of reducing them and stores its block count at
   // *defer_nb; otherwise it reduces as usual (products at out) and stores 0.
   // The Arnoldi update pass reduces deferred partials.
   double* defer = nullptr;
   int* defer_nb = nullptr;
+  const RideReduce* ride = nullptr;  // reduction carried by the operator's x-forward pass
 };
-// Largest block count of a pass whose products are left for deferred reduction.
-constexpr int kDeferMaxBlocks = 64;
+// Products are left for deferred reduction when the partials per value times
+// the blocks of the update pass, each of which sums them all, are at most this
+// (512^2: 512 x 1024).
+constexpr long long kDeferMaxSums = 1 << 19;
 
 // Delayed-CGS2 pass 2 of Arnoldi step j carried by the first x pass of the
 // operator of step j + 1 (k_xfwd_upd): with basis directions u_0 at u0 and

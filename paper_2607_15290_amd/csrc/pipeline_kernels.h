@@ -14,6 +14,7 @@
 // it is k_xfwd, k_axis(y, fwd), k_axis(z, fused), k_axis(y, inv), k_xinv.
 #pragma once
 #include "pipeline.h"
+#include "post.h"
 #include "wave.h"
 
 namespace llg {
@@ -463,13 +464,22 @@ template <typename T, typename TIn, int NH, int PRO, int SHAPE>
 __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xfwd(const TIn* __restrict__ in,
                                                                     const T* __restrict__ m,
                                                                     cx<T>* __restrict__ spec, SpecGeom g,
-                                                                    NodalArgs na, const cx<T>* __restrict__ twx) {
+                                                                    NodalArgs na, const cx<T>* __restrict__ twx,
+                                                                    RideReduce ride) {
   using C = XCfg<T, NH, SHAPE>;
   constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
+  if (ride.nv > 0 && blockIdx.x == 0) {
+    rows_sum<C::NT / 64>(ride.part, ride.nb, ride.nv, [&](int q, double s) {
+      ride.out[q] = s;
+      if (ride.post.flag) ride.post.mirror[q] = s;
+    });
+    post_block(ride.post);
+    return;
+  }
   const long long nlines = (long long)g.ny * g.nz;
-  const long long line0 = (long long)blockIdx.x * C::LX;
+  const long long line0 = (long long)(blockIdx.x - (ride.nv > 0 ? 1 : 0)) * C::LX;
   constexpr int NX = 2 * NH;
 
   // Copy-in with the prologue.  Indices are clamped instead of guarded so that

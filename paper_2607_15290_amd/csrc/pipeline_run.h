@@ -47,7 +47,8 @@ void with_x_shape(long long lines, F&& f) {
 }
 
 template <typename T, typename TIn, typename TOut, int NH, int PRO>
-void launch_xfwd(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& io, hipStream_t st) {
+void launch_xfwd(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& io, hipStream_t st,
+                 const BasisDots* bd = nullptr) {
   if constexpr (has_pro<T, TIn, TOut>(PRO)) {
     const long long lines = (long long)c.ny * c.nz;
     const cx<T>* tw;
@@ -55,8 +56,9 @@ void launch_xfwd(const Ctx& c, const NodalArgs& na, const PipeIO<T, TIn, TOut>& 
     const double in_b = PRO == PRO_COPY3 ? 3.0 * sizeof(TIn) : 4.0 * sizeof(TIn) + 3.0 * sizeof(T);
     ProfScope ps(c.prof, st, KK_XFWD, double(c.ng) * in_b + double(c.geom.cs) * lines * 2 * sizeof(T));
     with_x_shape<T, NH>(lines, [&](auto shape, unsigned grid, unsigned nt) {
-      hipLaunchKernelGGL((k_xfwd<T, TIn, NH, PRO, decltype(shape)::value>), dim3(grid), dim3(nt), 0, st, io.in, io.m,
-                         reinterpret_cast<cx<T>*>(c.spec), c.geom, na, tw);
+      const RideReduce ride = bd && bd->ride ? *bd->ride : RideReduce{};
+      hipLaunchKernelGGL((k_xfwd<T, TIn, NH, PRO, decltype(shape)::value>), dim3(grid + (ride.nv > 0 ? 1 : 0)), dim3(nt),
+                         0, st, io.in, io.m, reinterpret_cast<cx<T>*>(c.spec), c.geom, na, tw, ride);
     });
   }
 }
@@ -111,10 +113,7 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
   }
   const cx<T>* tw;
   if constexpr (std::is_same<T, double>::value) tw = c.tw_d[0]; else tw = c.tw_f[0];
-  // defer only over few blocks: every block of the update pass sums all of
-  // them (at 64 blocks one launch fewer per step gained 4%; at 256 the sums
-  // cost more than the launch)
-  const bool defer = bd.defer && grid <= unsigned(kDeferMaxBlocks);
+  const bool defer = bd.defer && (long long)grid * red_blocks(2 * c.ng) <= kDeferMaxSums;
   BasisDots kd = bd;
   kd.partial = defer ? bd.defer : c.partial;
   {
@@ -141,9 +140,9 @@ hipError_t run_nh(const Ctx& c, int pro, int epi, const SymArgs& sym, const Noda
   // never a silently skipped pass
   if (!has_pro<T, TIn, TOut>(pro) || !has_epi<T, TIn, TOut>(epi)) return hipErrorInvalidValue;
   switch (pro) {
-    case PRO_COPY3: launch_xfwd<T, TIn, TOut, NH, PRO_COPY3>(c, na, io, st); break;
-    case PRO_SMINUS: launch_xfwd<T, TIn, TOut, NH, PRO_SMINUS>(c, na, io, st); break;
-    case PRO_M2T: launch_xfwd<T, TIn, TOut, NH, PRO_M2T>(c, na, io, st); break;
+    case PRO_COPY3: launch_xfwd<T, TIn, TOut, NH, PRO_COPY3>(c, na, io, st, bd); break;
+    case PRO_SMINUS: launch_xfwd<T, TIn, TOut, NH, PRO_SMINUS>(c, na, io, st, bd); break;
+    case PRO_M2T: launch_xfwd<T, TIn, TOut, NH, PRO_M2T>(c, na, io, st, bd); break;
     case PRO_NONE: break;  // x spectra already in place (k_xfwd_upd)
     default: return hipErrorInvalidValue;
   }
@@ -213,7 +212,7 @@ hipError_t run_apply_matvec_nh(const Ctx& c, const SymArgs& sym_ap, const SymArg
                                double* dots_out, bool spec_ready, hipStream_t st) {
   PipeIO<float, double, float> io_ap{v, m32, z, c.ng, nullptr, nullptr};
   PipeIO<float, float, TW> io_mv{z, m32, w, c.ng, nullptr, nullptr};
-  if (!spec_ready) launch_xfwd<float, double, float, NH, PRO_COPY3>(c, na, io_ap, st);
+  if (!spec_ready) launch_xfwd<float, double, float, NH, PRO_COPY3>(c, na, io_ap, st, bd);
   hipError_t e;
   if ((e = run_axes<float>(c, sym_ap, st)) != hipSuccess) return e;
   {

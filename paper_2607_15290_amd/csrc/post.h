@@ -1,7 +1,7 @@
 // Device side of a Post (krylov.h): results of a reduction in the host's mapped
 // memory, announced by a flag that the host polls.
 #pragma once
-#include "krylov.h"
+#include "pipeline.h"
 
 namespace llg {
 

@@ -136,4 +136,28 @@ __device__ __forceinline__ void wave_sums_store(const double (&v)[N], double* __
   }
 }
 
+// Sums of nv rows of nb values (value-major) by the first NW wavefronts of a
+// block, four rows at a time per wavefront; dst(q, sum) on one lane per row.
+template <int NW, class F>
+__device__ __forceinline__ void rows_sum(const double* __restrict__ part, int nb, int nv, F&& dst) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int q0 = wv; q0 < nv; q0 += 4 * NW) {
+    const double* r[4];
+    double t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      r[k] = part + (long long)(q0 + k * NW < nv ? q0 + k * NW : q0) * nb;
+      t[k] = 0.0;
+    }
+#pragma unroll 4
+    for (int b = lane; b < nb; b += 64) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) t[k] += r[k][b];
+    }
+    const double s = wave_sums<4>(t);
+    const int q = q0 + wave_sums_index<4>(lane) * NW;
+    if ((lane & 15) == 0 && q < nv) dst(q, s);
+  }
+}
+
 }  // namespace llg

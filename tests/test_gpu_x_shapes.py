@@ -10,7 +10,7 @@ import torch
 
 import llg_workloads as W
 import paper_2607_15290_amd as P
-from oracle import operators
+from oracle import operators, steppers
 from oracle.grid import Grid
 from tests.gpu_util import announce, assert_elem, both_params, dev, host, unit_field
 
@@ -67,3 +67,30 @@ def test_products_in_every_shape(shape, nb):
     assert_elem(host(z), zr, lev * 2.0 ** -24, "z float32")
     check_dots(y, dots, "flexible float32")
     ctx.close()
+
+
+@pytest.mark.parametrize("shape", [
+    (16, 8, 1),       # one update block, pass-1 products and the pass-2 reduction both carried along
+    (512, 512, 1),    # the largest grid whose pass-2 reduction rides (1024 update blocks)
+    (128, 64, 48),    # 1536 update blocks: reductions of their own, operator still launched ahead
+])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_ir", "fp32_ir_left"])
+def test_cycles_across_reduction_rules(shape, prec):
+    """Solves on both sides of the rules that say where an Arnoldi step's
+    inner products are reduced, against the oracle's GMRES: solutions within
+    1e-8 (rtol 1e-10), float64 iteration counts within one."""
+    nx, ny, nz = shape
+    announce(f"reduction rules {shape} {prec}")
+    dt = W.dt_explicit_multiple(13.3, 0.05, max(nx, ny, nz), 2 if nz == 1 else 3)
+    prm, op = both_params(alpha=0.05, cexc=1.0, dt=dt, theta=0.5, shift=0.5, h_uniform=(0.0, 0.0, 1.0))
+    g = Grid(nx, ny, nz, h=1.0 / nx)
+    m = unit_field((nz, ny, nx), 51, smooth=12.0)
+    b = steppers.rhs(g, op, m)
+    xr, ir = steppers.solve_saddle(g, op, m, b, rtol=1e-10)
+    ctx = P.Context(nx, ny, nz, 1.0 / nx, 0)
+    x, st = P.gmres_solve(ctx, prm, dev(m), dev(b), rtol=1e-10, prec=prec, inner_rtol=1e-3)
+    ctx.close()
+    assert st["converged"] == 1
+    if prec == "fp64":
+        assert abs(st["iters"] - ir["iters"]) <= 1, (st, ir)
+    assert_elem(host(x), xr, 1e-8, "x")
