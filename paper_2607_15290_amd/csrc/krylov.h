@@ -83,6 +83,17 @@ inline int red_blocks(long long n2) {
   if (g > kRedBlocksMax) g = kRedBlocksMax;
   return int(g < 1 ? 1 : g);
 }
+// Node pairs of one plane that a block of the x passes owns (elements of
+// elem_bytes bytes), and the blocks of the small grids' update pass, which
+// shares out the same chunks over the XCDs (512 pairs of any plane each).
+inline unsigned x_pairs(int elem_bytes, const Ctx& c) {
+  const long long lines = (long long)c.ny * c.nz;
+  return unsigned(x_lx(elem_bytes, c.geom.nh, x_shape(elem_bytes, c.geom.nh, lines)) * c.geom.nh);
+}
+inline int small_update_blocks(long long ng, unsigned npair) {
+  const long long chunks = (ng / 2 + npair - 1) / npair, per_xcd = (chunks + 7) / 8;
+  return int(8 * ((per_xcd * 4 * npair + 2 * kRedThreads - 1) / (2 * kRedThreads)));
+}
 // out[0] = sum of c.partial[0 .. nb) (the x-inverse residual partials), posted
 hipError_t reduce_flat(const Ctx& c, int nb, double* out, hipStream_t st);
 // out[i] = V_i . w  (i < nv; V_i = V + i*ld)

@@ -340,6 +340,14 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
 // are in flight every block reduces the operator's unreduced pass-1 products
 // (dp, or reads the reduced p) and forms gamma itself.  No non-temporal hints:
 // the basis stays in the caches.
+//
+// XCD affinity.  An XCD's L2 keeps what it read or wrote across kernels: a
+// buffer of 32 MB re-read by the same XCDs arrives at 12.8 TB/s, by other
+// XCDs (and anything larger, from the Infinity Cache) at 5.8-6.9 TB/s.  The x
+// passes give their block b (XCD b % 8 under round-robin dispatch) the node
+// pairs [b npair, (b + 1) npair) of every plane; here block B takes a share
+// of the chunks c = B % 8 (mod 8) of that partition, so each basis vector is
+// read, and the new one written, by the XCD that the x passes use for it.
 template <int J, typename W2>
 __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update_small(const double2* __restrict__ u0,
                                                                   const double2* __restrict__ U1, long long ld2,
@@ -347,11 +355,15 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update_small(const double
                                                                   double2* __restrict__ unew, long long n2,
                                                                   double* __restrict__ partial, DcgsCoef cf,
                                                                   const double* __restrict__ p,
-                                                                  double* __restrict__ minv, DeferredDots dp) {
+                                                                  double* __restrict__ minv, DeferredDots dp,
+                                                                  unsigned npair) {
   __shared__ double gs[kDcgsMaxCols], pr[kDcgsMaxCols];
-  const long long e0 = (long long)blockIdx.x * kDcgsThreads + threadIdx.x;
-  const bool live = e0 < n2;
-  const long long e = live ? e0 : n2 - 1;
+  const unsigned local = blockIdx.x / 8 * kDcgsThreads + threadIdx.x;  // of the XCD's pairs of all four planes
+  const unsigned chunk = local / (4 * npair), within = local - chunk * 4 * npair;
+  const unsigned plane = within / npair;
+  const long long pair = (long long)(chunk * 8 + blockIdx.x % 8) * npair + (within - plane * npair);
+  const bool live = pair < n2 / 4;
+  const long long e = live ? plane * (n2 / 4) + pair : n2 - 1;
   const W2 wv = w[e];
   double2 q[J + 1];
   q[0] = u0[e];
@@ -595,19 +607,19 @@ static void dd_t(const Ctx& c, const double* u0, const double* U1, long long ld,
 template <int J, typename TW>
 static void du_t(const Ctx& c, const double* u0, const double* U1, long long ld, const double* gamma,
                  const DcgsCoef& cf, const double* p, const DeferredDots& dp, const TW* w, double* unew, long long n,
-                 hipStream_t st) {
+                 unsigned grid, unsigned npair, hipStream_t st) {
   constexpr unsigned lds = std::is_same<TW, float>::value ? LLG_DCGS_UPDATE_LDS_F32W : LLG_DCGS_UPDATE_LDS;
-  const dim3 grid(red_blocks(n / 2)), block(kDcgsThreads);
+  const dim3 block(kDcgsThreads);
   const double2* a0 = reinterpret_cast<const double2*>(u0);
   const double2* a1 = reinterpret_cast<const double2*>(U1);
   const pair_of<TW>* wp = reinterpret_cast<const pair_of<TW>*>(w);
   double2* un = reinterpret_cast<double2*>(unew);
   if (gamma)
-    hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>>), grid, block, lds, st, a0, a1, ld / 2, gamma, cf.inv_beta, wp,
+    hipLaunchKernelGGL((k_dcgs_update<J, pair_of<TW>>), dim3(grid), block, lds, st, a0, a1, ld / 2, gamma, cf.inv_beta, wp,
                        un, n / 2, c.partial);
   else
-    hipLaunchKernelGGL((k_dcgs_update_small<J, pair_of<TW>>), grid, block, 0, st, a0, a1, ld / 2, wp, un, n / 2,
-                       c.partial, cf, p, c.tri, dp);
+    hipLaunchKernelGGL((k_dcgs_update_small<J, pair_of<TW>>), dim3(grid), block, 0, st, a0, a1, ld / 2, wp, un,
+                       n / 2, c.partial, cf, p, c.tri, dp, npair);
 }
 
 // Runtime J -> template instantiation J = 0..kDcgsMaxCols - 1.
@@ -674,12 +686,18 @@ static hipError_t dcgs_update_t(const Ctx& c, const double* u0, const double* U1
     hipError_t e = dcgs_coef(c, cf, p, &gamma, st);
     if (e != hipSuccess) return e;
   }
-  const int nb = red_blocks(n / 2);
-  if (!gamma && (long long)nb * kDcgsThreads < n / 2) return hipErrorInvalidValue;
+  unsigned npair = 0;
+  int nb = red_blocks(n / 2);
+  if (!gamma) {
+    if (n != 4 * c.ng) return hipErrorInvalidValue;
+    npair = x_pairs(sizeof(TW), c);
+    nb = small_update_blocks(c.ng, npair);
+    if (nb > kRedBlocksMax) return hipErrorInvalidValue;
+  }
   {
     // j + 1 directions read, w read, u_new written
     ProfScope ps(c.prof, st, KK_CGS_UPDATE_DOTS, double(n) * (8.0 * (cf.j + 2) + sizeof(TW)));
-    JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, st);
+    JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, unsigned(nb), npair, st);
   }
   const Post post = next_post(c, out, p, cf.j + 1);
   if (ride && nb <= kRideMaxBlocks) {

@@ -190,7 +190,7 @@ struct Post {
   unsigned long long seq = 0;
 };
 // A reduction (nv rows of nb block partials, value-major, into out and the
-// Post) that rides in the next x-forward pass as its block 0: on small grids
+// Post) that rides in the next x-forward pass as its last block: on small grids
 // it takes the place of a launch of its own between two passes.
 struct RideReduce {
   const double* part = nullptr;
@@ -198,7 +198,7 @@ struct RideReduce {
   double* out = nullptr;
   Post post;
 };
-constexpr int kRideMaxBlocks = 1024;
+constexpr int kRideMaxBlocks = 1100;  // 512^2: 1024 (and the rounding up per XCD)
 
 // Arnoldi inner products taken by an x-inverse pass on its own output (the
 // precision form's matvec): with basis directions u_0 at u0 and u_i at

@@ -113,7 +113,7 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
   }
   const cx<T>* tw;
   if constexpr (std::is_same<T, double>::value) tw = c.tw_d[0]; else tw = c.tw_f[0];
-  const bool defer = bd.defer && (long long)grid * red_blocks(2 * c.ng) <= kDeferMaxSums;
+  const bool defer = bd.defer && (long long)grid * small_update_blocks(c.ng, x_pairs(int(sizeof(T)), c)) <= kDeferMaxSums;
   BasisDots kd = bd;
   kd.partial = defer ? bd.defer : c.partial;
   {
