@@ -6,21 +6,40 @@
 
 namespace llg {
 
+// Passes with fewer wide blocks than this take the narrow shape.
+#ifndef LLG_AXIS_NARROW_BLOCKS
+#define LLG_AXIS_NARROW_BLOCKS 256
+#endif
+
+template <typename T, int N, bool NARROW>
+static void axis_launch(const Ctx& c, int axis, int mode, const SymArgs& sym, cx<T>* spec, const cx<T>* tw,
+                        hipStream_t st) {
+  using C = AxisCfg<T, N, NARROW>;
+  const dim3 grid((unsigned)((c.geom.cs + C::W - 1) / C::W), (unsigned)(axis == 1 ? c.nz : c.ny));
+  const dim3 block(C::W * C::TPL);
+  switch (mode) {
+    case 0: hipLaunchKernelGGL((k_axis<T, N, 0, NARROW>), grid, block, 0, st, spec, c.geom, axis, sym, tw); break;
+    case 1: hipLaunchKernelGGL((k_axis<T, N, 1, NARROW>), grid, block, 0, st, spec, c.geom, axis, sym, tw); break;
+    default: hipLaunchKernelGGL((k_axis<T, N, 2, NARROW>), grid, block, 0, st, spec, c.geom, axis, sym, tw); break;
+  }
+}
+
 template <typename T, int N>
 static hipError_t axis_n(const Ctx& c, int axis, int mode, const SymArgs& sym, cx<T>* spec, hipStream_t st) {
-  constexpr int W = axis_w(int(sizeof(T)), N), TPL = N / plan_p(axis_plan_key(int(sizeof(T)), N));
-  const unsigned gx = (unsigned)((c.geom.cs + W - 1) / W);
-  const unsigned gy = (unsigned)(axis == 1 ? c.nz : c.ny);
+  constexpr int W = AxisCfg<T, N, false>::W;
+  const long long blocks = (long long)((c.geom.cs + W - 1) / W) * (axis == 1 ? c.nz : c.ny);
   const cx<T>* tw;
   if constexpr (std::is_same<T, double>::value) tw = c.tw_d[axis];
   else tw = c.tw_f[axis];
   const double bytes = 2.0 * c.geom.cs * double(c.ny) * c.nz * 2 * sizeof(T);
   ProfScope ps(c.prof, st, mode == 0 ? KK_AXIS_FWD : (mode == 1 ? KK_AXIS_INV : KK_AXIS_FUSED), bytes);
-  switch (mode) {
-    case 0: hipLaunchKernelGGL((k_axis<T, N, 0>), dim3(gx, gy), dim3(W * TPL), 0, st, spec, c.geom, axis, sym, tw); break;
-    case 1: hipLaunchKernelGGL((k_axis<T, N, 1>), dim3(gx, gy), dim3(W * TPL), 0, st, spec, c.geom, axis, sym, tw); break;
-    default: hipLaunchKernelGGL((k_axis<T, N, 2>), dim3(gx, gy), dim3(W * TPL), 0, st, spec, c.geom, axis, sym, tw); break;
+  if constexpr (AxisCfg<T, N, true>::W < W) {
+    if (blocks < LLG_AXIS_NARROW_BLOCKS) {
+      axis_launch<T, N, true>(c, axis, mode, sym, spec, tw, st);
+      return hipGetLastError();
+    }
   }
+  axis_launch<T, N, false>(c, axis, mode, sym, spec, tw, st);
   return hipGetLastError();
 }
 

@@ -788,11 +788,14 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
       off[i] = f * io.ng + line * NX + 2 * xp;
       w[i] = it0 < NITEM ? lds_o[it] : cx<T>{T(0), T(0)};
     }
-    for (int q0 = wv; q0 < bd.nv; q0 += NW * QB) {
+    // last column first: the update pass before this one ended with the last
+    // columns and the one after it starts with the first, so each pass finds
+    // in the L2s what the other touched last
+    for (int q0 = bd.nv - 1 - wv; q0 >= 0; q0 -= NW * QB) {
       double a0[QB][NIT], a1[QB][NIT];
 #pragma unroll
       for (int k = 0; k < QB; ++k) {
-        const int q = q0 + k * NW < bd.nv ? q0 + k * NW : q0;
+        const int q = q0 - k * NW >= 0 ? q0 - k * NW : q0;
         const double* col = q == 0 ? bd.u0 : bd.U1 + (q - 1) * bd.ld;
 #pragma unroll
         for (int i = 0; i < NIT; ++i) load2<NT>(col + off[i], a0[k][i], a1[k][i]);
@@ -805,8 +808,8 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn
         for (int i = 0; i < NIT; ++i) t[k] = fma(a0[k][i], double(w[i].x), fma(a1[k][i], double(w[i].y), t[k]));
       }
       const double s = wave_sums<QB>(t);
-      const int k = wave_sums_index<QB>(lane), q = q0 + k * NW;
-      if ((lane & (64 / wave_pow2(QB) - 1)) == 0 && k < QB && q < bd.nv)
+      const int k = wave_sums_index<QB>(lane), q = q0 - k * NW;
+      if ((lane & (64 / wave_pow2(QB) - 1)) == 0 && k < QB && q >= 0)
         bd.partial[(long long)q * gridDim.x + blockIdx.x] = s;
     }
   } else if constexpr (DOTS) {
@@ -957,11 +960,21 @@ __host__ __device__ constexpr int axis_w(int elem_bytes, int n) {
                                                              : ((n & (n - 1)) != 0 && n <= 24 ? 64 : 16)));
 }
 
-template <typename T, int N, int MODE>
-__global__ __launch_bounds__(axis_w(int(sizeof(T)), N) * (N / plan_p(axis_plan_key(int(sizeof(T)), N)))) void k_axis(
+// Launch shape: W columns per block, or with NARROW the fewest that fill a
+// wavefront (at least 4), for grids whose passes have fewer blocks than CUs.
+template <typename T, int N, bool NARROW>
+struct AxisCfg {
+  static constexpr int KEY = axis_plan_key(int(sizeof(T)), N);
+  static constexpr int P = plan_p(KEY), TPL = N / P, WIDE = axis_w(int(sizeof(T)), N);
+  static constexpr int FEW = TPL >= 16 ? 4 : 64 / TPL;
+  static constexpr int W = NARROW && FEW < WIDE ? FEW : WIDE;
+};
+
+template <typename T, int N, int MODE, bool NARROW>
+__global__ __launch_bounds__((AxisCfg<T, N, NARROW>::W * AxisCfg<T, N, NARROW>::TPL)) void k_axis(
     cx<T>* __restrict__ spec, SpecGeom g, int axis, SymArgs sym, const cx<T>* __restrict__ tw) {
-  constexpr int KEY = axis_plan_key(int(sizeof(T)), N);
-  constexpr int P = plan_p(KEY), TPL = N / P, W = axis_w(int(sizeof(T)), N);
+  using C = AxisCfg<T, N, NARROW>;
+  constexpr int KEY = C::KEY, P = C::P, TPL = C::TPL, W = C::W;
   __shared__ cx<T> lds[N * (W + 1)];
   const int c = threadIdx.x % W, t = threadIdx.x / W;
   // XCD-aware block numbering.  Blocks are dispatched to the 8 XCDs (each

@@ -94,3 +94,27 @@ def test_cycles_across_reduction_rules(shape, prec):
     if prec == "fp64":
         assert abs(st["iters"] - ir["iters"]) <= 1, (st, ir)
     assert_elem(host(x), xr, 1e-8, "x")
+
+
+@pytest.mark.parametrize("n", [64, 128, 160, 192, 256, 320, 384, 512])
+@pytest.mark.parametrize("axis", ["y", "z"])
+def test_wide_axis_passes(n, axis):
+    """Axis lengths with two launch shapes, on grids with enough blocks for the
+    wide one (the operator tests' small grids take the narrow one): A x and
+    M^{-1} x in float64 (1e-12) and float32 (one unit roundoff per butterfly
+    level)."""
+    nx, ny, nz = (32, n, 96) if axis == "y" else (32, 96, n)
+    announce(f"wide axis passes {axis} {n}")
+    dt = W.dt_explicit_multiple(13.3, 0.02, max(nx, ny, nz), 3)
+    prm, op = both_params(alpha=0.02, cexc=1.0, dt=dt, theta=0.5, shift=0.5, h_uniform=(0.0, 0.0, 1.0))
+    g = Grid(nx, ny, nz, h=1.0 / nx)
+    m = unit_field((nz, ny, nx), 61, smooth=40.0)
+    x = np.random.default_rng(62).standard_normal((4, nz, ny, nx))
+    ctx = P.Context(nx, ny, nz, 1.0 / nx, 0)
+    assert_elem(host(P.llg_matvec(ctx, prm, dev(m), dev(x))), operators.matvec(g, op, m, x), 1e-12, "A x")
+    assert_elem(host(P.fft_hss_apply(ctx, prm, dev(m), dev(x))), operators.hss_apply(g, op, m, x), 1e-12, "M^-1 x")
+    mf, xf = dev(m, torch.float32), dev(x, torch.float32)
+    tol = (sum(2 * int(np.ceil(np.log2(k))) for k in (nx, ny, nz)) + 16) * 2.0 ** -24
+    assert_elem(host(P.fft_hss_apply_f32(ctx, prm, mf, xf)), operators.hss_apply(g, op, host(mf), host(xf)), tol,
+                "M^-1 x float32")
+    ctx.close()
