@@ -56,11 +56,14 @@ __device__ __forceinline__ cx<T> mul_dir_i(cx<T> a) {
 //   N:   2   4   8  16  32    64    128    256     512      1024
 //   R:  [2] [4] [8][16][8,4] [8,8] [16,8] [16,16] [8,8,8] [16,16,4]
 // Lengths 3 * 2^k and 5 * 2^k (the grids N = 24, 48 of the paper's 3D
-// experiments, among others) keep the odd factor inside P:
-//   N:   3   5   6     10    12    20    24    40 (P 20)  48 (P 12)  80 (P 20)
-//   R:  [3] [5] [2,3] [2,5] [4,3] [4,5] [8,3] [4,2,5]    [4,4,3]    [4,4,5]
+// experiments, among others) keep the odd factor inside P, in a first stage
+// of composite radix (6 = 2 x 3, 10 = 2 x 5, 12 = 4 x 3, 20 = 4 x 5, 24 = 8 x 3,
+// in registers): one LDS exchange and one set of twiddles fewer than with the
+// odd factor as a stage of its own, and none at all up to N = 24.
+//   N:   3   5   6   10   12   20   24   40 (P 20)  48 (P 12)  80 (P 20)
+//   R:  [3] [5] [6] [10] [12] [20] [24] [10,4]     [12,4]     [20,4]
 //   N:   96 (P 24)  160 (P 20)  192 (P 24)  320 (P 20)  384 (P 24)
-//   R:  [8,4,3]    [4,4,2,5]   [8,8,3]     [4,4,4,5]   [8,4,4,3]
+//   R:  [12,8]     [10,4,4]    [24,8]      [20,4,4]    [12,8,4]
 // ---------------------------------------------------------------------------
 // A plan key is the line length N, or N | kPlanFine for a plan with fewer
 // points per thread (more threads per line, one more LDS exchange): the
@@ -79,25 +82,25 @@ __host__ __device__ constexpr Plan plan_of(int n) {
     case 3: return {3, 1, 3, 1, 1, 1};
     case 4: return {4, 1, 4, 1, 1, 1};
     case 5: return {5, 1, 5, 1, 1, 1};
-    case 6: return {6, 2, 2, 3, 1, 1};
+    case 6: return {6, 1, 6, 1, 1, 1};
     case 8: return {8, 1, 8, 1, 1, 1};
-    case 10: return {10, 2, 2, 5, 1, 1};
-    case 12: return {12, 2, 4, 3, 1, 1};
+    case 10: return {10, 1, 10, 1, 1, 1};
+    case 12: return {12, 1, 12, 1, 1, 1};
     case 16: return {16, 1, 16, 1, 1, 1};
-    case 20: return {20, 2, 4, 5, 1, 1};
-    case 24: return {24, 2, 8, 3, 1, 1};
+    case 20: return {20, 1, 20, 1, 1, 1};
+    case 24: return {24, 1, 24, 1, 1, 1};
     case 32: return {8, 2, 8, 4, 1, 1};
-    case 40: return {20, 3, 4, 2, 5, 1};
-    case 48: return {12, 3, 4, 4, 3, 1};
+    case 40: return {20, 2, 10, 4, 1, 1};
+    case 48: return {12, 2, 12, 4, 1, 1};
     case 64: return {8, 2, 8, 8, 1, 1};
-    case 80: return {20, 3, 4, 4, 5, 1};
-    case 96: return {24, 3, 8, 4, 3, 1};
+    case 80: return {20, 2, 20, 4, 1, 1};
+    case 96: return {24, 2, 12, 8, 1, 1};
     case 128: return {16, 2, 16, 8, 1, 1};
-    case 160: return {20, 4, 4, 4, 2, 5};
-    case 192: return {24, 3, 8, 8, 3, 1};
+    case 160: return {20, 3, 10, 4, 4, 1};
+    case 192: return {24, 2, 24, 8, 1, 1};
     case 256: return {16, 2, 16, 16, 1, 1};
-    case 320: return {20, 4, 4, 4, 4, 5};
-    case 384: return {24, 4, 8, 4, 4, 3};
+    case 320: return {20, 3, 20, 4, 4, 1};
+    case 384: return {24, 3, 12, 8, 4, 1};
     case 512: return {8, 3, 8, 8, 8, 1};
     case 1024: return {16, 3, 16, 16, 4, 1};
     default: return {0, 0, 1, 1, 1, 1};
@@ -131,7 +134,8 @@ __device__ __forceinline__ constexpr int out_q(int slot) {
 }
 
 // ---------------------------------------------------------------------------
-// In-register DFTs of size 2, 3, 4, 5, 8, 16 (natural order in and out).
+// In-register DFTs of size 2, 3, 4, 5, 8, 16 and the composite sizes (natural
+// order in and out).
 // ---------------------------------------------------------------------------
 template <typename T, int DIR>
 __device__ __forceinline__ void dft2(cx<T>& a, cx<T>& b) {
@@ -265,6 +269,72 @@ __device__ __forceinline__ void dft5(cx<T>* v) {
   v[3] = csub(a2, b2);
 }
 
+// cos(2 pi k / 24) and cos(2 pi k / 20), exact to the last digit of a double
+__host__ __device__ constexpr double cos24(int k) {
+  constexpr double c[7] = {1.0, 0.96592582628906828674974319972889736763, 0.86602540378443864676372317075293618347,
+                           0.70710678118654752440084436210484903928, 0.5, 0.25881904510252076234889883762404832834,
+                           0.0};
+  k = ((k % 24) + 24) % 24;
+  if (k > 12) k = 24 - k;
+  return k <= 6 ? c[k] : -c[12 - k];
+}
+__host__ __device__ constexpr double cos20(int k) {
+  constexpr double c[6] = {1.0, 0.95105651629515357211643933337938214340, 0.80901699437494742410229341718281905886,
+                           0.58778525229247312916870595463907276859, 0.30901699437494742410229341718281905886, 0.0};
+  k = ((k % 20) + 20) % 20;
+  if (k > 10) k = 20 - k;
+  return k <= 5 ? c[k] : -c[10 - k];
+}
+// multiply by exp(DIR 2 pi i E / N), N = 6, 10, 12, 20 or 24 (compile time)
+template <typename T, int DIR, int N, int E>
+__device__ __forceinline__ cx<T> wn(cx<T> a) {
+  constexpr bool five = N % 5 == 0;
+  constexpr int L = five ? 20 : 24, e = (E * (L / N)) % L;
+  if constexpr (e == 0) return a;
+  else if constexpr (4 * e == L) return mul_dir_i<T, DIR>(a);
+  else if constexpr (2 * e == L) return {-a.x, -a.y};
+  else if constexpr (4 * e == 3 * L) return mul_dir_i<T, -DIR>(a);
+  else {
+    constexpr T wr = T(five ? cos20(e) : cos24(e));
+    constexpr T ws = T(five ? cos20(e - 5) : cos24(e - 6));  // sin
+    constexpr T wi = DIR < 0 ? -ws : ws;
+    return {a.x * wr - a.y * wi, a.x * wi + a.y * wr};
+  }
+}
+
+template <typename T, int R, int DIR>
+__device__ __forceinline__ void dft(cx<T>* v);
+
+// DFT of size A B (A = 2, 4 or 8; B = 3 or 5) in registers: with n = a + A b and
+// k = k2 + B k1, DFTs of size B over b, twiddles w^(a k2), DFTs of size A over a.
+template <typename T, int A, int B, int DIR, int I = 0>
+__device__ __forceinline__ void comp_twiddle(cx<T> (&y)[A][B]) {
+  if constexpr (I < A * B) {
+    y[I / B][I % B] = wn<T, DIR, A * B, (I / B) * (I % B)>(y[I / B][I % B]);
+    comp_twiddle<T, A, B, DIR, I + 1>(y);
+  }
+}
+template <typename T, int A, int B, int DIR>
+__device__ __forceinline__ void dft_comp(cx<T>* v) {
+  cx<T> y[A][B];
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) y[a][b] = v[a + A * b];
+    dft<T, B, DIR>(y[a]);
+  }
+  comp_twiddle<T, A, B, DIR>(y);
+#pragma unroll
+  for (int k2 = 0; k2 < B; ++k2) {
+    cx<T> x[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) x[a] = y[a][k2];
+    dft<T, A, DIR>(x);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) v[k2 + B * k1] = x[k1];
+  }
+}
+
 template <typename T, int R, int DIR>
 __device__ __forceinline__ void dft(cx<T>* v) {
   if constexpr (R == 1) {
@@ -273,7 +343,9 @@ __device__ __forceinline__ void dft(cx<T>* v) {
   else if constexpr (R == 4) dft4<T, DIR>(v[0], v[1], v[2], v[3]);
   else if constexpr (R == 5) dft5<T, DIR>(v);
   else if constexpr (R == 8) dft8<T, DIR>(v);
-  else dft16<T, DIR>(v);
+  else if constexpr (R == 16) dft16<T, DIR>(v);
+  else if constexpr (R % 3 == 0) dft_comp<T, R / 3, 3, DIR>(v);
+  else dft_comp<T, R / 5, 5, DIR>(v);
 }
 
 // ---------------------------------------------------------------------------
