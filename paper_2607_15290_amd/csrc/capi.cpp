@@ -254,11 +254,21 @@ llg_status fetch(const Ctx& c, const double* dev, int n, hipStream_t st, double*
 // ---- workspace -----------------------------------------------------------
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
+// Stride of the Krylov vectors in the workspace, in elements of elem_bytes
+// bytes.  Vectors of power-of-two grids are a power of two apart, and an
+// Arnoldi pass reads the same place of every one of them at once: 20 KB more
+// on grids whose basis streams from HBM spread those reads over the channels
+// (256^3 float64 solve 134.3 -> 127.4 ms; 4 KB 127.6, 8.25 KB 128.7, 1 MB
+// 129.9; the precision forms and 128^3 gain up to 1%).
+long long basis_ld(const Ctx& c, int elem_bytes) {
+  return 4 * c.ng + (c.ng > kSpeculateMaxNodes ? 20480 / elem_bytes : 0);
+}
+
 struct Work {
-  double* V = nullptr;   // (R + 2) x n4: basis (R + 1 columns) and the Arnoldi operator output
+  double* V = nullptr;   // (R + 2) columns at stride basis_ld: basis (R + 1) and the Arnoldi operator output
   double* r = nullptr;   // n4
   double* t = nullptr;   // n4 temporary
-  float* Z = nullptr;    // R x n4 (precision form)
+  float* Z = nullptr;    // R columns at stride basis_ld (precision form)
   float* m32 = nullptr;  // 3 ng   (precision form)
   float* W32 = nullptr;  // n4     (precision form: the float32 operator output of an Arnoldi step)
   double* b = nullptr;   // n4  stepper right-hand side
@@ -281,10 +291,10 @@ Work carve(const Ctx& c, int R, int prec, void* base) {
     off += align256(bytes);
     return q;
   };
-  w.V = reinterpret_cast<double*>(take(sizeof(double) * n4 * (R + 2)));
+  w.V = reinterpret_cast<double*>(take(sizeof(double) * basis_ld(c, 8) * (R + 2)));
   w.r = reinterpret_cast<double*>(take(sizeof(double) * n4));
   w.t = reinterpret_cast<double*>(take(sizeof(double) * n4));
-  if (prec == LLG_FP32_IR) w.Z = reinterpret_cast<float*>(take(sizeof(float) * n4 * R));
+  if (prec == LLG_FP32_IR) w.Z = reinterpret_cast<float*>(take(sizeof(float) * basis_ld(c, 4) * R));
   if (prec != LLG_FP64) w.m32 = reinterpret_cast<float*>(take(sizeof(float) * n3));
   if (prec != LLG_FP64) w.W32 = reinterpret_cast<float*>(take(sizeof(float) * n4));
   w.b = reinterpret_cast<double*>(take(sizeof(double) * n4));
@@ -341,12 +351,12 @@ struct Hess {
 
 // One Arnoldi step on V_{j+1} (already holding the new direction): CGS2 against
 // V_0..V_j, normalization, column of H.  Returns status; fills col[0..j+1].
-llg_status arnoldi_step(const Ctx& c, double* V, long long n4, int j, double* col, hipStream_t st) {
-  double* w = V + size_t(j + 1) * n4;
+llg_status arnoldi_step(const Ctx& c, double* V, long long ld, long long n4, int j, double* col, hipStream_t st) {
+  double* w = V + size_t(j + 1) * ld;
   const int nv = j + 1;
-  CHK(cgs_dots(c, V, n4, nv, w, n4, c.dots, st));
-  CHK(cgs_update_dots(c, V, n4, nv, c.dots, w, n4, c.dots2, st));
-  CHK(cgs_update_norm(c, V, n4, nv, c.dots2, w, w, n4, c.scal, st));
+  CHK(cgs_dots(c, V, ld, nv, w, n4, c.dots, st));
+  CHK(cgs_update_dots(c, V, ld, nv, c.dots, w, n4, c.dots2, st));
+  CHK(cgs_update_norm(c, V, ld, nv, c.dots2, w, w, n4, c.scal, st));
   double hv[3 * kMaxDots];
   CHK(hipMemcpyAsync(c.host, c.dots, sizeof(double) * 3 * kMaxDots, hipMemcpyDeviceToHost, st));
   CHK(hipStreamSynchronize(st));
@@ -364,7 +374,7 @@ llg_status arnoldi_step(const Ctx& c, double* V, long long n4, int j, double* co
 // iteration.
 //
 // The device holds the raw directions U = [u_0 .. u_j] (u_0 = the start
-// vector, not normalized, at u0; u_i, i >= 1, at U1 + (i - 1) n4); the
+// vector, not normalized, at u0; u_i, i >= 1, at U1 + (i - 1) ld); the
 // orthonormal basis is Q = U T^{-1}, T upper triangular with column j =
 // [a; beta_j].  Entering iteration j the host knows a = Q_j^T u_j and beta_j
 // = ||u_j - Q_j a|| (from the previous update pass), which finalizes column
@@ -420,7 +430,7 @@ struct FirstUpd {
 
 template <typename TW>
 llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, const double* u0, double* U1, TW* W,
-                       long long n4, double c0, int R, double eta, int maxiter, int& iters, CycleResult& out,
+                       long long ld, long long n4, double c0, int R, double eta, int maxiter, int& iters, CycleResult& out,
                        hipStream_t st, const FirstUpd<TW>* fu = nullptr) {
   if (R >= kDcgsMaxCols) return fail(LLG_EARG, "delayed CGS2 needs restart <= 31");
   Hess hs(R);
@@ -451,10 +461,10 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
   // Operator of step jj on u_jj into W, its pass-1 products into pslot.
   hipError_t op_err = hipSuccess;
   auto launch_op = [&](int jj, double* pslot, bool spec_ready) {
-    const double* ujj = jj == 0 ? u0 : U1 + size_t(jj - 1) * n4;
+    const double* ujj = jj == 0 ? u0 : U1 + size_t(jj - 1) * ld;
     hipError_t e;
     if (op_dots) {
-      BasisDots bq{u0, U1, n4, jj + 1, nullptr};
+      BasisDots bq{u0, U1, ld, jj + 1, nullptr};
       bq.out = pslot;
       if (defer) {
         bq.defer = defer_part;
@@ -464,7 +474,7 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
       e = op(jj, ujj, W, &bq, spec_ready);
     } else {
       e = op(jj, ujj, W, nullptr, spec_ready);
-      if (e == hipSuccess) e = dcgs_dots(c, u0, U1, n4, jj, W, n4, pslot, st);
+      if (e == hipSuccess) e = dcgs_dots(c, u0, U1, ld, jj, W, n4, pslot, st);
     }
     if (e != hipSuccess && op_err == hipSuccess) op_err = e;
   };
@@ -504,10 +514,10 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
       UpdFirst ua;
       ua.u0 = u0;
       ua.U1 = U1;
-      ua.ld = n4;
+      ua.ld = ld;
       ua.j = j;
       ua.inv_beta = cf.inv_beta;
-      ua.unew = U1 + size_t(j) * n4;
+      ua.unew = U1 + size_t(j) * ld;
       ua.partial = c.partial;
       ua.p = pslot;
       CHK(dcgs_coef(c, cf, pslot, &ua.gamma, st));
@@ -520,7 +530,7 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
         dd.out = pslot;
       }
       ride = RideReduce{};
-      CHK(dcgs_update(c, u0, U1, n4, cf, pslot, W, U1 + size_t(j) * n4, n4, c.dots2, st, &dd,
+      CHK(dcgs_update(c, u0, U1, ld, cf, pslot, W, U1 + size_t(j) * ld, n4, c.dots2, st, &dd,
                       defer && more ? &ride : nullptr));
     }
     // one round trip: the pass-1 dots p and the pass-2 dots of u_{j+1}, which
@@ -607,7 +617,7 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
                       const llg_solver_opts& o, Work& w, SolveResult& res, hipStream_t st,
                       const OpDots* MAd = nullptr, const SolveHints& hints = {},
                       const FirstUpd<double>* fu = nullptr) {
-  const long long n4 = 4 * c.ng;
+  const long long n4 = 4 * c.ng, ld = basis_ld(c, 8);
   const int R = o.restart;
   double bnorm = hints.bnorm;
   if (bnorm < 0) {
@@ -654,7 +664,7 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
     if (o.orth == 0) {
       // basis directions u_0 .. u_R in columns 0 .. R of V, Op output in column R + 1
       double* U0 = w.V;
-      double* W = w.V + size_t(R + 1) * n4;
+      double* W = w.V + size_t(R + 1) * ld;
       CHK(M(w.r, U0));
       double un[2];
       CHK(dot_and_norm(c, U0, nullptr, n4, c.scal, st));
@@ -663,13 +673,13 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
       auto op = [&](int, const double* u, double* wout, const BasisDots* bq, bool ready) {
         return MAd ? (*MAd)(u, wout, bq, ready) : MA(u, wout);
       };
-      CHK_STATUS(cycle_dcgs2<double>(c, op, MAd != nullptr && LLG_FUSE_DOTS != 0, U0, U0 + n4, W, n4, un[1], R,
+      CHK_STATUS(cycle_dcgs2<double>(c, op, MAd != nullptr && LLG_FUSE_DOTS != 0, U0, U0 + ld, W, ld, n4, un[1], R,
                                      target / rho, o.maxiter, res.iters, cr, st, MAd ? fu : nullptr));
       if (!is_fin(cr.beta0)) return fail(LLG_ENAN, "non-finite preconditioned residual");
       if (beta0 < 0) beta0 = cr.beta0;
       res.rel_prec = beta0 > 0 ? cr.gres / beta0 : 0.0;
       if (cr.k == 0) break;
-      CHK(lincomb(c, n4, cr.y, U0, n4, x, st));
+      CHK(lincomb(c, n4, cr.y, U0, ld, x, st));
       CHK(RA(x, b, w.r));
       CHK_STATUS(fetch(c, c.scal, 1, st, rn));
       rho = std::sqrt(rn[0]);
@@ -689,8 +699,8 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
     hs.g[0] = beta;
     int k = 0;
     for (int j = 0; j < R; ++j) {
-      CHK(MA(w.V + size_t(j) * n4, w.V + size_t(j + 1) * n4));
-      CHK_STATUS(arnoldi_step(c, w.V, n4, j, col.data(), st));
+      CHK(MA(w.V + size_t(j) * ld, w.V + size_t(j + 1) * ld));
+      CHK_STATUS(arnoldi_step(c, w.V, ld, n4, j, col.data(), st));
       const double gres = hs.add_column(j, col.data());
       res.iters++;
       k = j + 1;
@@ -699,7 +709,7 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
     }
     Coefs y{};
     hs.solve(k, y);
-    CHK(lincomb(c, n4, y, w.V, n4, x, st));
+    CHK(lincomb(c, n4, y, w.V, ld, x, st));
     CHK(RA(x, b, w.r));
     CHK_STATUS(fetch(c, c.scal, 1, st, rn));
     rho = std::sqrt(rn[0]);
@@ -717,7 +727,7 @@ llg_status gmres_left(const Ctx& c, const ResidOp& RA, const Op& M, const Op& MA
 llg_status gmres_right(const Ctx& c, const ResidOp& RA, const Op& M, const OpDots& AMd, const double* b, double* x,
                        const llg_solver_opts& o, Work& w, SolveResult& res, hipStream_t st,
                        const FirstUpd<double>* fu = nullptr) {
-  const long long n4 = 4 * c.ng;
+  const long long n4 = 4 * c.ng, ld = basis_ld(c, 8);
   const int R = o.restart;
   double nb[2];
   CHK(dot_and_norm(c, b, nullptr, n4, c.scal, st));
@@ -746,7 +756,7 @@ llg_status gmres_right(const Ctx& c, const ResidOp& RA, const Op& M, const OpDot
   res.r_valid = true;
   // u_0 = r (raw), u_1 .. u_R in columns 0 .. R - 1 of V, operator output in
   // column R + 1 (also the preconditioned update at the cycle's end)
-  double* W = w.V + size_t(R + 1) * n4;
+  double* W = w.V + size_t(R + 1) * ld;
   while (true) {
     if (!is_fin(rho)) return fail(LLG_ENAN, "non-finite residual");
     res.rel_true = rho / bnorm;
@@ -760,7 +770,7 @@ llg_status gmres_right(const Ctx& c, const ResidOp& RA, const Op& M, const OpDot
     auto op = [&](int, const double* u, double* wout, const BasisDots* bq, bool ready) {
       return AMd(u, wout, bq, ready);
     };
-    CHK_STATUS(cycle_dcgs2<double>(c, op, LLG_FUSE_DOTS != 0, w.r, w.V, W, n4, rho * rho, R, target / rho, o.maxiter,
+    CHK_STATUS(cycle_dcgs2<double>(c, op, LLG_FUSE_DOTS != 0, w.r, w.V, W, ld, n4, rho * rho, R, target / rho, o.maxiter,
                                    res.iters, cr, st, fu));
     res.rel_prec = cr.gres / bnorm;
     if (cr.k == 0) break;
@@ -770,7 +780,7 @@ llg_status gmres_right(const Ctx& c, const ResidOp& RA, const Op& M, const OpDot
       Coefs rest{};
       rest.n = cr.k - 1;
       for (int i = 1; i < cr.k; ++i) rest.c[i - 1] = cr.y.c[i];
-      CHK(lincomb(c, n4, rest, w.V, n4, w.t, st));
+      CHK(lincomb(c, n4, rest, w.V, ld, w.t, st));
     }
     CHK(M(w.t, W));
     CHK(axpby(c, n4, 1.0, x, 1.0, W, x, st));
@@ -788,7 +798,7 @@ llg_status gmres_right(const Ctx& c, const ResidOp& RA, const Op& M, const OpDot
 // (LLG_FP32_IR_LEFT, one float32 pipeline per inner iteration).
 llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const double* b, double* x,
                     const llg_solver_opts& o, Work& w, SolveResult& res, hipStream_t st, const SolveHints& hints) {
-  const long long n4 = 4 * c.ng;
+  const long long n4 = 4 * c.ng, ld = basis_ld(c, 8), ldz = basis_ld(c, 4);
   const int R = o.restart;
   if (!hints.m32_ready) CHK(to_f32(c, 3 * c.ng, m, w.m32, st));
   const SymArgs sym_ap = sym_for(c, p->alpha + p->shift, hcoef(p), true);
@@ -845,7 +855,7 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
       // basis in columns 0 .. R of V (delayed CGS2: raw directions; classic
       // CGS2: orthonormal vectors), Op output in column R + 1
       double* Q = w.V;
-      double* W = w.V + size_t(R + 1) * n4;
+      double* W = w.V + size_t(R + 1) * ld;
       PipeIO<float, double, double> io_m{w.r, w.m32, Q, c.ng, nullptr, nullptr};
       CHK((run_pipeline<float, double, double>(c, PRO_COPY3, EPI_APPLY, sym_ap, na, io_m, st)));
       double un[2];
@@ -869,7 +879,7 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
             [&](const UpdFirst& ua, const float* wv, double* out) {
               return run_xfwd_upd(c, PRO_SMINUS, na, ua, wv, w.m32, out, st);
             }};
-        CHK_STATUS(cycle_dcgs2<float>(c, opl32, LLG_FUSE_DOTS != 0, Q, Q + n4, w.W32, n4, un[1], R, eta,
+        CHK_STATUS(cycle_dcgs2<float>(c, opl32, LLG_FUSE_DOTS != 0, Q, Q + ld, w.W32, ld, n4, un[1], R, eta,
                                       o.maxiter, res.iters, cr, st, &fu));
       } else {
         const double beta = std::sqrt(un[1]);
@@ -880,8 +890,8 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
         hs.g[0] = beta;
         cr.beta0 = beta;
         for (int j = 0; j < R; ++j) {
-          CHK(opl(j, Q + size_t(j) * n4, Q + size_t(j + 1) * n4, nullptr));
-          CHK_STATUS(arnoldi_step(c, Q, n4, j, col.data(), st));
+          CHK(opl(j, Q + size_t(j) * ld, Q + size_t(j + 1) * ld, nullptr));
+          CHK_STATUS(arnoldi_step(c, Q, ld, n4, j, col.data(), st));
           cr.gres = hs.add_column(j, col.data());
           res.iters++;
           cr.k = j + 1;
@@ -891,7 +901,7 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
       }
       res.rel_prec = cr.beta0 > 0 ? cr.gres / cr.beta0 : 0.0;
       if (cr.k == 0) break;
-      CHK(lincomb(c, n4, cr.y, Q, n4, x, st));
+      CHK(lincomb(c, n4, cr.y, Q, ld, x, st));
       CHK(RA(x, b, w.r));
       CHK_STATUS(fetch(c, c.scal, 1, st, rn));
       rho = std::sqrt(rn[0]);
@@ -903,7 +913,7 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
       // operator output in float32 (W32): the float32 matvec's values exactly
       ArnoldiOpT<float> op = [&](int j, const double* u, float* wout, const BasisDots* bq,
                                  bool ready) -> hipError_t {
-        return run_apply_matvec(c, sym_ap, sym_mv, na, u, w.m32, w.Z + size_t(j) * n4, wout, st, bq, c.dots,
+        return run_apply_matvec(c, sym_ap, sym_mv, na, u, w.m32, w.Z + size_t(j) * ldz, wout, st, bq, c.dots,
                                 ready);
       };
       const FirstUpd<float> fu{
@@ -912,11 +922,11 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
             return run_xfwd_upd(c, PRO_COPY3, na, ua, wv, w.m32, out, st);
           }};
       CycleResult cr;
-      CHK_STATUS(cycle_dcgs2<float>(c, op, LLG_FUSE_DOTS != 0, w.r, w.V, w.W32, n4, rho * rho, R, eta, o.maxiter,
+      CHK_STATUS(cycle_dcgs2<float>(c, op, LLG_FUSE_DOTS != 0, w.r, w.V, w.W32, ld, n4, rho * rho, R, eta, o.maxiter,
                                     res.iters, cr, st, &fu));
       res.rel_prec = cr.gres / bnorm;
       if (cr.k == 0) break;
-      CHK(lincomb(c, n4, cr.y, w.Z, n4, x, st));
+      CHK(lincomb(c, n4, cr.y, w.Z, ldz, x, st));
       CHK(RA(x, b, w.r));
       CHK_STATUS(fetch(c, c.scal, 1, st, rn));
       rho = std::sqrt(rn[0]);
@@ -927,9 +937,9 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
     hs.g[0] = rho;
     int k = 0;
     for (int j = 0; j < R; ++j) {
-      CHK(run_apply_matvec(c, sym_ap, sym_mv, na, w.V + size_t(j) * n4, w.m32, w.Z + size_t(j) * n4,
-                           w.V + size_t(j + 1) * n4, st));
-      CHK_STATUS(arnoldi_step(c, w.V, n4, j, col.data(), st));
+      CHK(run_apply_matvec(c, sym_ap, sym_mv, na, w.V + size_t(j) * ld, w.m32, w.Z + size_t(j) * ldz,
+                           w.V + size_t(j + 1) * ld, st));
+      CHK_STATUS(arnoldi_step(c, w.V, ld, n4, j, col.data(), st));
       const double gres = hs.add_column(j, col.data());
       res.iters++;
       k = j + 1;
@@ -938,7 +948,7 @@ llg_status gmres_ir(const Ctx& c, const llg_params* p, const double* m, const do
     }
     Coefs y{};
     hs.solve(k, y);
-    CHK(lincomb(c, n4, y, w.Z, n4, x, st));
+    CHK(lincomb(c, n4, y, w.Z, ldz, x, st));
     CHK(RA(x, b, w.r));
     CHK_STATUS(fetch(c, c.scal, 1, st, rn));
     rho = std::sqrt(rn[0]);
