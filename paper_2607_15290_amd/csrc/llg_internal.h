@@ -154,4 +154,11 @@ hipError_t run_field(const Ctx& c, const FieldArgs& fa, int epi, const NodalArgs
 template <typename T>
 hipError_t launch_axis(const Ctx& c, int axis, int mode, const SymArgs& sym, cx<T>* spec, hipStream_t st);
 
+// The three axis passes of a 3-D pipeline in one kernel (plane.hip), on grids
+// for which plane_ok.
+template <typename T>
+bool plane_ok(const Ctx& c);
+template <typename T>
+hipError_t launch_plane(const Ctx& c, const SymArgs& sym, cx<T>* spec, hipStream_t st);
+
 }  // namespace llg

@@ -133,6 +133,19 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
   return reduce_partials_n(c, int(grid), bd.nv, dots_out, st);
 }
 
+// Axis passes of one pipeline on the spectral buffer: y forward, z fused,
+// y inverse (3D; one kernel on small grids) or y fused (2D).
+template <typename T>
+hipError_t run_axes(const Ctx& c, const SymArgs& sym, hipStream_t st) {
+  cx<T>* spec = reinterpret_cast<cx<T>*>(c.spec);
+  hipError_t e;
+  if (plane_ok<T>(c)) return launch_plane<T>(c, sym, spec, st);
+  if (c.dim == 2) return launch_axis<T>(c, 1, 2, sym, spec, st);
+  if ((e = launch_axis<T>(c, 1, 0, sym, spec, st)) != hipSuccess) return e;
+  if ((e = launch_axis<T>(c, 2, 2, sym, spec, st)) != hipSuccess) return e;
+  return launch_axis<T>(c, 1, 1, sym, spec, st);
+}
+
 template <typename T, typename TIn, typename TOut, int NH>
 hipError_t run_nh(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
                   const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd, double* dots_out) {
@@ -146,15 +159,8 @@ hipError_t run_nh(const Ctx& c, int pro, int epi, const SymArgs& sym, const Noda
     case PRO_NONE: break;  // x spectra already in place (k_xfwd_upd)
     default: return hipErrorInvalidValue;
   }
-  cx<T>* spec = reinterpret_cast<cx<T>*>(c.spec);
-  hipError_t e;
-  if (c.dim == 2) {
-    if ((e = launch_axis<T>(c, 1, 2, sym, spec, st)) != hipSuccess) return e;
-  } else {
-    if ((e = launch_axis<T>(c, 1, 0, sym, spec, st)) != hipSuccess) return e;
-    if ((e = launch_axis<T>(c, 2, 2, sym, spec, st)) != hipSuccess) return e;
-    if ((e = launch_axis<T>(c, 1, 1, sym, spec, st)) != hipSuccess) return e;
-  }
+  const hipError_t e = run_axes<T>(c, sym, st);
+  if (e != hipSuccess) return e;
   if (bd && bd->nv > 0) {
     if (bd->out) dots_out = bd->out;
     // the Arnoldi inner products ride on the fused preconditioned passes only
@@ -185,18 +191,6 @@ hipError_t run_nh(const Ctx& c, int pro, int epi, const SymArgs& sym, const Noda
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-// Axis passes of one pipeline on the spectral buffer: y forward, z fused,
-// y inverse (3D) or y fused (2D).
-template <typename T>
-hipError_t run_axes(const Ctx& c, const SymArgs& sym, hipStream_t st) {
-  cx<T>* spec = reinterpret_cast<cx<T>*>(c.spec);
-  hipError_t e;
-  if (c.dim == 2) return launch_axis<T>(c, 1, 2, sym, spec, st);
-  if ((e = launch_axis<T>(c, 1, 0, sym, spec, st)) != hipSuccess) return e;
-  if ((e = launch_axis<T>(c, 2, 2, sym, spec, st)) != hipSuccess) return e;
-  return launch_axis<T>(c, 1, 1, sym, spec, st);
 }
 
 // One inner iteration's operator of the precision form: z = M^{-1} v in

@@ -118,3 +118,29 @@ def test_wide_axis_passes(n, axis):
     assert_elem(host(P.fft_hss_apply_f32(ctx, prm, mf, xf)), operators.hss_apply(g, op, host(mf), host(xf)), tol,
                 "M^-1 x float32")
     ctx.close()
+
+
+PLANE_LENGTHS = [4, 6, 8, 10, 12, 16, 20, 24, 32]
+
+
+@pytest.mark.parametrize("ny", PLANE_LENGTHS)
+def test_plane_kernel(ny):
+    """The one-kernel axis passes of small 3-D grids on every pair of lengths
+    they take (and, at the larger pairs, on the three passes just above the
+    rule): M^{-1} x in float64 (1e-12) and float32 (one unit roundoff per
+    butterfly level)."""
+    nx = 12
+    for nz in PLANE_LENGTHS:
+        announce(f"plane kernel {nx}x{ny}x{nz}")
+        dt = W.dt_explicit_multiple(13.3, 0.02, max(nx, ny, nz), 3)
+        prm, op = both_params(alpha=0.02, cexc=1.0, dt=dt, theta=0.5, shift=0.5, h_uniform=(0.0, 0.0, 1.0))
+        g = Grid(nx, ny, nz, h=1.0 / nx)
+        m = unit_field((nz, ny, nx), 81, smooth=40.0)
+        x = np.random.default_rng(82).standard_normal((4, nz, ny, nx))
+        ctx = P.Context(nx, ny, nz, 1.0 / nx, 0)
+        assert_elem(host(P.fft_hss_apply(ctx, prm, dev(m), dev(x))), operators.hss_apply(g, op, m, x), 1e-12, "f64")
+        mf, xf = dev(m, torch.float32), dev(x, torch.float32)
+        tol = (sum(2 * int(np.ceil(np.log2(k))) for k in (nx, ny, nz)) + 16) * 2.0 ** -24
+        assert_elem(host(P.fft_hss_apply_f32(ctx, prm, mf, xf)), operators.hss_apply(g, op, host(mf), host(xf)), tol,
+                    "f32")
+        ctx.close()
