@@ -1111,11 +1111,8 @@ llg_status llg_ctx_create_cell(llg_ctx** out, int nx, int ny, int nz, double lx,
   if (hipMalloc(&c.spec, c.spec_bytes) != hipSuccess) return cleanup(LLG_ENOMEM, "spectral scratch allocation failed");
   if (hipMalloc(&c.partial, sizeof(double) * kRedBlocksMax * kMaxDots) != hipSuccess)
     return cleanup(LLG_ENOMEM, "reduction buffer allocation failed");
-  if (hipMalloc(&c.dots, sizeof(double) * (kDotsSlots * kMaxDots + 1)) != hipSuccess)
+  if (hipMalloc(&c.dots, sizeof(double) * kDotsSlots * kMaxDots) != hipSuccess)
     return cleanup(LLG_ENOMEM, "reduction buffer allocation failed");
-  c.post_count = reinterpret_cast<unsigned*>(c.dots + kDotsSlots * kMaxDots);
-  if (hipMemset(c.post_count, 0, sizeof(double)) != hipSuccess)
-    return cleanup(LLG_EHIP, "reduction buffer initialisation failed");
   c.dots2 = c.dots + kMaxDots;
   c.scal = c.dots + 2 * kMaxDots;
   c.dots_b = c.dots + 4 * kMaxDots;
@@ -1130,24 +1127,38 @@ llg_status llg_ctx_create_cell(llg_ctx** out, int nx, int ny, int nz, double lx,
   if (hipHostMalloc(reinterpret_cast<void**>(&c.host), sizeof(double) * 4 * kMaxDots, hipHostMallocDefault) !=
       hipSuccess)
     return cleanup(LLG_ENOMEM, "pinned host buffer allocation failed");
+  // The twiddle tables of all axes and the zeroed counter of the Posts are one
+  // allocation and one copy: each call to the runtime here costs 10-50 us,
+  // a large part of what a small context takes to make.
   const int ns[3] = {nx, ny, nz};
+  constexpr size_t kLine = 128;
+  size_t off_d[3], off_f[3], bytes = kLine;  // the counter has a line of its own
+  for (int a = 0; a < 3; ++a) {
+    if (ns[a] < 2) continue;
+    off_d[a] = bytes;
+    bytes += (sizeof(cx<double>) * ns[a] + kLine - 1) / kLine * kLine;
+    off_f[a] = bytes;
+    bytes += (sizeof(cx<float>) * ns[a] + kLine - 1) / kLine * kLine;
+  }
+  if (hipMalloc(&c.tables, bytes) != hipSuccess) return cleanup(LLG_ENOMEM, "twiddle allocation failed");
+  std::vector<char> host(bytes, 0);
+  char* dev = static_cast<char*>(c.tables);
+  c.post_count = reinterpret_cast<unsigned*>(dev);
   for (int a = 0; a < 3; ++a) {
     const int n = ns[a];
     if (n < 2) continue;
-    std::vector<cx<double>> td(n);
-    std::vector<cx<float>> tf(n);
+    c.tw_d[a] = reinterpret_cast<cx<double>*>(dev + off_d[a]);
+    c.tw_f[a] = reinterpret_cast<cx<float>*>(dev + off_f[a]);
     for (int m = 0; m < n; ++m) {
       const long double ang = -2.0L * 3.14159265358979323846264338327950288L * (long double)m / (long double)n;
-      td[m] = {(double)cosl(ang), (double)sinl(ang)};
-      tf[m] = {(float)cosl(ang), (float)sinl(ang)};
+      const cx<double> td = {(double)cosl(ang), (double)sinl(ang)};
+      const cx<float> tf = {(float)cosl(ang), (float)sinl(ang)};
+      std::memcpy(host.data() + off_d[a] + sizeof(td) * m, &td, sizeof(td));
+      std::memcpy(host.data() + off_f[a] + sizeof(tf) * m, &tf, sizeof(tf));
     }
-    if (hipMalloc(&c.tw_d[a], sizeof(cx<double>) * n) != hipSuccess ||
-        hipMalloc(&c.tw_f[a], sizeof(cx<float>) * n) != hipSuccess)
-      return cleanup(LLG_ENOMEM, "twiddle allocation failed");
-    if (hipMemcpy(c.tw_d[a], td.data(), sizeof(cx<double>) * n, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(c.tw_f[a], tf.data(), sizeof(cx<float>) * n, hipMemcpyHostToDevice) != hipSuccess)
-      return cleanup(LLG_EHIP, "twiddle upload failed");
   }
+  if (hipMemcpy(c.tables, host.data(), bytes, hipMemcpyHostToDevice) != hipSuccess)
+    return cleanup(LLG_EHIP, "twiddle upload failed");
   *out = ctx;
   return LLG_OK;
 }
@@ -1167,10 +1178,7 @@ llg_status llg_ctx_destroy(llg_ctx* ctx) {
   (void)hipGetDevice(&cur);
   if (cur != c.device) (void)hipSetDevice(c.device);
   (void)hipDeviceSynchronize();
-  for (int a = 0; a < 3; ++a) {
-    if (c.tw_d[a]) (void)hipFree(c.tw_d[a]);
-    if (c.tw_f[a]) (void)hipFree(c.tw_f[a]);
-  }
+  if (c.tables) (void)hipFree(c.tables);
   if (c.spec) (void)hipFree(c.spec);
   if (c.partial) (void)hipFree(c.partial);
   if (c.dots) (void)hipFree(c.dots);

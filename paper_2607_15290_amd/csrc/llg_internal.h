@@ -61,6 +61,7 @@ struct Ctx {
   double Lx = 0, Ly = 0, Lz = 0;  // cell lengths (spacing L / n per axis)
   long long ng = 0;
   SpecGeom geom{};
+  void* tables = nullptr;  // one allocation: post_count and the tables below
   cx<double>* tw_d[3] = {nullptr, nullptr, nullptr};  // exp(-2 pi i m / n_axis)
   cx<float>* tw_f[3] = {nullptr, nullptr, nullptr};
   void* spec = nullptr;  // spectral scratch (complex double capacity)
