@@ -18,7 +18,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libllg.so")
 SOURCES = ["pipeline_f64_hi.hip", "pipeline_f64_lo.hip", "pipeline_mixed_hi.hip", "pipeline_mixed_lo.hip",
            "pipeline_f32_hi.hip", "pipeline_f32_lo.hip", "apply_matvec.hip", "field.hip", "krylov.hip",
-           "xfwd_upd.hip", "plane.hip", "axis.hip", "nodal.hip", "capi.cpp", "noalloc.hip", "profiler.cpp"]
+           "xfwd_upd.hip", "plane.hip", "grid2d.hip", "axis.hip", "nodal.hip", "capi.cpp", "noalloc.hip", "profiler.cpp"]
 ARCH = "gfx950"
 # packed fp32 ops are disabled for every device compile; hipcc's host pass
 # reports the feature as unknown, which is harmless.

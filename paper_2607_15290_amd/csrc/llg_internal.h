@@ -162,4 +162,12 @@ bool plane_ok(const Ctx& c);
 template <typename T>
 hipError_t launch_plane(const Ctx& c, const SymArgs& sym, cx<T>* spec, hipStream_t st);
 
+// A whole 2-D pipeline in one kernel (grid2d.hip), on the grids and for the
+// modes for which grid2d_ok; not the residual form.
+template <typename T>
+bool grid2d_ok(const Ctx& c, int pro, int epi);
+template <typename T>
+hipError_t launch_grid2d(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
+                         const PipeIO<T, T, T>& io, hipStream_t st);
+
 }  // namespace llg

@@ -233,6 +233,9 @@ hipError_t run_apply_matvec_nh(const Ctx& c, const SymArgs& sym_ap, const SymArg
 template <typename T, typename TIn, typename TOut, bool HI>
 hipError_t run_pipeline_part(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na,
                              const PipeIO<T, TIn, TOut>& io, hipStream_t st, const BasisDots* bd, double* dots_out) {
+  if constexpr (!HI && std::is_same<T, TIn>::value && std::is_same<T, TOut>::value) {
+    if (!bd && !io.rhs && grid2d_ok<T>(c, pro, epi)) return launch_grid2d<T>(c, pro, epi, sym, na, io, st);
+  }
 #define LLG_CASE(n) \
   case n: return run_nh<T, TIn, TOut, n>(c, pro, epi, sym, na, io, st, bd, dots_out);
   if constexpr (HI) {

@@ -7,6 +7,7 @@
 // costs its 3-4 us whatever it moves.  A block reads one value of each row
 // (16 or 8 bytes of a 128-byte line), so each XCD takes a contiguous range of
 // columns and finds its neighbours' lines in its L2.
+#include "lds_lines.h"
 #include "llg_internal.h"
 #include "pipeline_kernels.h"
 
@@ -18,38 +19,12 @@ constexpr int kPlaneThreads = 256;
 // LDS line stride: odd, so that lanes on neighbouring lines hit different banks
 __host__ __device__ constexpr int plane_stride(int ny) { return ny + 1 - ny % 2; }
 
-// All lines along one axis of the block's column, DFT of length N in
-// direction DIR.  Lines are spread over the lanes first.  in(line, pos) and
-// out(line, pos, value) move a value; at(line, pos) is its LDS slot.
-template <typename T, int N, int DIR, class At, class In, class Out>
-__device__ __forceinline__ void plane_lines(int nlines, const cx<T>* __restrict__ tw, At&& at, In&& in, Out&& out) {
-  constexpr int P = plan_p(N), TPL = N / P, L = kPlaneThreads / TPL;
-  const int ln = threadIdx.x % L, t = threadIdx.x / L;
-  for (int l0 = 0; l0 < nlines; l0 += L) {  // the same trips for every thread (barriers inside)
-    const bool on = l0 + ln < nlines;
-    const int line = on ? l0 + ln : 0;
-    cx<T> v[P];
-    if (on) {
-#pragma unroll
-      for (int q = 0; q < P; ++q) v[in_slot<N>(q)] = in(line, t + TPL * q);
-    }
-    auto acc = [&](int pos) -> cx<T>& { return at(line, pos); };
-    line_fft<T, N, DIR>(v, t, acc, tw, 1, on);
-    __syncthreads();  // a later stage's reads before the values are replaced
-    if (on) {
-#pragma unroll
-      for (int s = 0; s < P; ++s) out(line, t + TPL * out_q<N>(s), v[s]);
-    }
-  }
-  __syncthreads();
-}
-
 template <typename T, int DIR, class At, class In, class Out>
 __device__ __forceinline__ void plane_axis(int n, int nlines, const cx<T>* __restrict__ tw, At&& at, In&& in,
                                            Out&& out) {
   switch (n) {  // plane_ok: n is one of them
 #define LLG_CASE(v) \
-  case v: plane_lines<T, v, DIR>(nlines, tw, at, in, out); break;
+  case v: lds_lines<T, v, DIR, kPlaneThreads>(nlines, tw, 1, at, in, out); break;
     LLG_FOR_PLANE(LLG_CASE)
 #undef LLG_CASE
   }
