@@ -167,12 +167,14 @@ bool grid_modes(int pro, int epi) {
 }
 }  // namespace
 
-// Largest grid: 1536 nodes in float64, 3072 in float32.  M^{-1} x, three passes
-// against one kernel: float64 24^2 15.6 -> 9.3 us, 48 x 32 15.6 -> 13.4, 48^2
-// 15.6 -> 17.7, 64^2 14.6 -> 27.5; float32 32^2 15.6 -> 8.7, 48^2 15.7 ->
-// 12.8, 64^2 15.7 -> 18.6.  The passes of a solve's Arnoldi steps stay three
-// kernels: their last one reads the whole basis, which needs many CUs.
-constexpr size_t kGridBytes = 12288;
+// Largest grid: 1280 nodes in float64, 2560 in float32.  M^{-1} x, three passes
+// against one kernel: float64 24^2 15.6 -> 9.3 us, 32^2 15.8 -> 10.6, 48 x 32
+// 15.6 -> 13.4 (but 13.3 us of GPU time against 12.9), 48^2 15.6 -> 17.7, 64^2
+// 14.6 -> 27.5; float32 32^2 15.6 -> 8.7, 48^2 15.7 -> 12.8, 64 x 48
+// transposed 15.4 -> 16.9, 64^2 15.7 -> 18.6.  The passes of a solve's Arnoldi
+// steps stay three kernels: their last one reads the whole basis, which needs
+// many CUs.
+constexpr size_t kGridBytes = 10240;
 template <typename T>
 bool grid2d_ok(const Ctx& c, int pro, int epi) {
   return c.dim == 2 && size_t(c.ng) * sizeof(T) <= kGridBytes && grid_length(c.geom.nh, c.ny) && grid_modes(pro, epi);

@@ -114,7 +114,7 @@ hipError_t run_pipeline(const Ctx& c, int pro, int epi, const SymArgs& sym, cons
   return run_pipeline_part<T, TIn, TOut, true>(c, pro, epi, sym, na, io, st, bd, dots_out);
 }
 
-// Precision-form inner operator (pipeline_f32.hip): z = M^{-1} v (float32,
+// Precision-form inner operator (apply_matvec.hip): z = M^{-1} v (float32,
 // stored) and w = A z (float32, float64 result), the two pipelines joined by
 // one fused x pass.  With bd (bd->nv > 0) the last pass also forms the
 // Arnoldi inner products dots_out[q] = u_q . w, q < bd->nv (device).

@@ -72,8 +72,13 @@ inline unsigned x_blocks(int elem_bytes, int nh, long long lines, int shape, boo
   const int lx = x_lx(elem_bytes, nh, shape, dots);
   return unsigned((lines + lx - 1) / lx);
 }
-// Shape of the x passes on a grid: wide above LLG_X_WIDE_BLOCKS wide blocks,
-// otherwise the mid shape if it gives a block to nearly every CU.
+// Shape of the x passes on a grid: wide above LLG_X_WIDE_BLOCKS wide blocks
+// (one per CU), otherwise the mid shape if it gives a block to nearly every
+// CU.  With the line at 1024 blocks 160 x 96 x 80 solves (640) took 11% longer:
+// there the passes are bound by bytes, and 80 of 256 threads hold a line.
+// Below 256 the wide shape leaves CUs idle: 48^3 solves (36 blocks) 6.5 -> 4.3
+// ms with the mid shape, 32^2 Euler steps (1 block) 23.5 -> 16.7 with the
+// small one, 512^2 (64 blocks) the same with both.
 #ifndef LLG_X_WIDE_BLOCKS
 #define LLG_X_WIDE_BLOCKS 256
 #endif

@@ -12,6 +12,8 @@
 //
 // In two dimensions a pipeline is k_xfwd, k_axis(y, fused), k_xinv; in three
 // it is k_xfwd, k_axis(y, fwd), k_axis(z, fused), k_axis(y, inv), k_xinv.
+// On small grids k_plane takes the place of the three axis passes (plane.hip),
+// k_grid2d that of a whole 2-D pipeline (grid2d.hip).
 #pragma once
 #include "pipeline.h"
 #include "post.h"
