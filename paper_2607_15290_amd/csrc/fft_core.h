@@ -67,11 +67,8 @@ __device__ __forceinline__ cx<T> mul_dir_i(cx<T> a) {
 // ---------------------------------------------------------------------------
 // A plan key is the line length N, or N | kPlanFine for a plan with fewer
 // points per thread (more threads per line, one more LDS exchange): the
-// float64 x passes use it at N = 128, 256 to halve their LDS per block; or
-// N | kPlanCoarse for one with more points per thread (more lines per block):
-// the x-inverse passes with Arnoldi products (x_plan_key).
+// float64 x passes use it at N = 128, 256 to halve their LDS per block.
 constexpr int kPlanFine = 1 << 16;
-constexpr int kPlanCoarse = 1 << 17;
 __host__ __device__ constexpr int plan_n(int key) { return key & (kPlanFine - 1); }
 
 struct Plan {
@@ -79,8 +76,6 @@ struct Plan {
 };
 __host__ __device__ constexpr Plan plan_of(int n) {
   switch (n) {
-    case 32 | kPlanCoarse: return {16, 2, 16, 2, 1, 1};
-    case 64 | kPlanCoarse: return {16, 2, 16, 4, 1, 1};
     case 128 | kPlanFine: return {8, 3, 8, 4, 4, 1};
     case 256 | kPlanFine: return {8, 3, 8, 8, 4, 1};
     case 2: return {2, 1, 2, 1, 1, 1};

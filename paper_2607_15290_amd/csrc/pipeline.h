@@ -41,17 +41,7 @@ constexpr int kNhLoMax = 32;  // the pipelines of the two halves are separate tr
 // FFT plan key of the x passes for elements of elem_bytes bytes and half-length
 // nh: the float64 passes at nh = 128, 256 take the finer plan (fewer points
 // per thread, half the LDS per block; see kPlanFine).
-//
-// With Arnoldi products (dots) a block reads its nodes of every basis vector,
-// one chunk per plane and column: blocks of 512 pairs read 8 KB at a time,
-// which the memory serves at 5.2 TB/s where 16-20 KB chunks reach 6.5-7.
-// These passes take the plan with more points per thread, and so twice the
-// lines per block, where their FFT phase can afford it: 128^3 left-form
-// solves 9.05 -> 8.94 ms, 512 x 64 x 64 float64 16.7 -> 16.2, 64 x 256 x 128
-// 16.7 -> 16.5 (not float64 at nh = 128: 256^3 134.4 -> 135.8).
-__host__ __device__ constexpr int x_plan_key(int elem_bytes, int nh, bool dots = false) {
-  if (dots && (nh == 32 || nh == 64)) return nh | kPlanCoarse;
-  if (dots && nh == 256) return nh;
+__host__ __device__ constexpr int x_plan_key(int elem_bytes, int nh) {
   return (elem_bytes == 8 && (nh == 128 || nh == 256)) ? (nh | kPlanFine) : nh;
 }
 
@@ -61,15 +51,15 @@ __host__ __device__ constexpr int x_plan_key(int elem_bytes, int nh, bool dots =
 // which only load, store and reduce, on the rows that hold about 256 or 64
 // node pairs, so that grids of few rows still reach every CU.
 enum XShape : int { X_WIDE = 0, X_MID = 1, X_SMALL = 2 };
-__host__ __device__ constexpr int x_lx(int elem_bytes, int nh, int shape, bool dots = false) {
-  const int tpl = nh / plan_p(x_plan_key(elem_bytes, nh, dots && shape == X_WIDE));
+__host__ __device__ constexpr int x_lx(int elem_bytes, int nh, int shape) {
+  const int tpl = nh / plan_p(x_plan_key(elem_bytes, nh));
   if (shape == X_WIDE) return 64 / tpl;
   const int pairs = shape == X_MID ? 256 : 64, most = 64 / tpl;
   const int lx = nh >= pairs ? 1 : pairs / nh;
   return lx < most ? lx : most;
 }
-inline unsigned x_blocks(int elem_bytes, int nh, long long lines, int shape, bool dots = false) {
-  const int lx = x_lx(elem_bytes, nh, shape, dots);
+inline unsigned x_blocks(int elem_bytes, int nh, long long lines, int shape) {
+  const int lx = x_lx(elem_bytes, nh, shape);
   return unsigned((lines + lx - 1) / lx);
 }
 // Shape of the x passes on a grid: wide above LLG_X_WIDE_BLOCKS wide blocks

@@ -24,12 +24,12 @@ namespace llg {
 // Launch shape of the x passes for element type T and half-length NH.  The
 // float64 passes at NH = 128, 256 use the finer plan (8 points per thread):
 // half the lines per block, half the LDS, twice the blocks per CU.
-template <typename T, int NH, int SHAPE = X_WIDE, bool DOTS = false>
+template <typename T, int NH, int SHAPE = X_WIDE>
 struct XCfg {
-  static constexpr int KEY = x_plan_key(int(sizeof(T)), NH, DOTS && SHAPE == X_WIDE);
+  static constexpr int KEY = x_plan_key(int(sizeof(T)), NH);
   static constexpr int P = plan_p(KEY);
   static constexpr int TPL = NH / P;
-  static constexpr int LX = x_lx(int(sizeof(T)), NH, SHAPE, DOTS);  // rows per block
+  static constexpr int LX = x_lx(int(sizeof(T)), NH, SHAPE);  // rows per block
   static constexpr int NDFT = 3 * LX * TPL;                    // threads that hold a part of a line
   static constexpr int NT = SHAPE == X_WIDE ? NDFT : 256;
   static constexpr int SL = NH + (NH >> 4) + 1; // LDS line stride (complex)
@@ -409,11 +409,11 @@ __device__ __forceinline__ void x_r2c_store(cx<T>* lds, long long line0, long lo
 // step (Z[k] = (U[k] + conj U[NH-k]) + i w^{-k} (U[k] - conj U[NH-k])) and run
 // the inverse half-length DFT; on return LDS position k of each line holds the
 // node pair (2k, 2k+1) of each field.
-template <typename T, int NH, int SHAPE = X_WIDE, bool DOTS = false>
+template <typename T, int NH, int SHAPE = X_WIDE>
 __device__ __forceinline__ void x_load_c2r(cx<T>* lds, long long line0, long long nlines,
                                            const cx<T>* __restrict__ spec, const SpecGeom& g,
                                            const cx<T>* __restrict__ twx) {
-  using C = XCfg<T, NH, SHAPE, DOTS>;
+  using C = XCfg<T, NH, SHAPE>;
   const int tid = threadIdx.x;
   constexpr int CS = 3 * (NH + 1);
   {
@@ -679,13 +679,13 @@ __global__ __launch_bounds__(192) void k_xfwd_upd(UpdFirst ua, const W* __restri
 // alone.  On a cache-resident grid the pass is bound by the latency of its
 // serial chain (load, sum, next column), not by bytes.
 template <typename T, typename TIn, typename TOut, int NH, int EPI, bool DOTS, int SHAPE>
-__global__ __launch_bounds__((XCfg<T, NH, SHAPE, DOTS>::NT)) void k_xinv(PipeIO<T, TIn, TOut> io,
+__global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xinv(PipeIO<T, TIn, TOut> io,
                                                                     const cx<T>* __restrict__ spec, SpecGeom g,
                                                                     NodalArgs na, const cx<T>* __restrict__ twx,
                                                                     BasisDots bd) {
   static_assert(!DOTS || EPI == EPI_MATVEC || EPI == EPI_FUSED || EPI == EPI_JT_RIGHT,
                 "dots: Krylov output of a matvec or fused pass");
-  using C = XCfg<T, NH, SHAPE, DOTS>;
+  using C = XCfg<T, NH, SHAPE>;
   constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   __shared__ cx<T> lds_o[DOTS && SHAPE != X_WIDE ? 4 * C::LX * NH : 1];  // output pairs, plane-major
@@ -695,7 +695,7 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE, DOTS>::NT)) void k_xinv(PipeIO<
   constexpr int NX = 2 * NH;
   constexpr int CS = 3 * (NH + 1);
 
-  x_load_c2r<T, NH, SHAPE, DOTS>(lds, line0, nlines, spec, g, twx);
+  x_load_c2r<T, NH, SHAPE>(lds, line0, nlines, spec, g, twx);
 
   // Epilogue: clamped (unconditional) loads issued a batch of node pairs at
   // a time, predicated stores.

@@ -32,17 +32,17 @@ constexpr bool has_epi(int epi) {
 
 // Calls f(integral_constant shape, blocks, threads) with the x passes' launch
 // shape on this grid (x_shape).
-template <typename T, int NH, int SHAPE, bool DOTS, class F>
+template <typename T, int NH, int SHAPE, class F>
 void x_launch(long long lines, F&& f) {
-  f(std::integral_constant<int, SHAPE>{}, x_blocks(int(sizeof(T)), NH, lines, SHAPE, DOTS),
-    unsigned(XCfg<T, NH, SHAPE, DOTS>::NT));
+  f(std::integral_constant<int, SHAPE>{}, x_blocks(int(sizeof(T)), NH, lines, SHAPE),
+    unsigned(XCfg<T, NH, SHAPE>::NT));
 }
-template <typename T, int NH, bool DOTS = false, class F>
+template <typename T, int NH, class F>
 void with_x_shape(long long lines, F&& f) {
   switch (x_shape(int(sizeof(T)), NH, lines)) {
-    case X_WIDE: x_launch<T, NH, X_WIDE, DOTS>(lines, f); break;
-    case X_MID: x_launch<T, NH, X_MID, DOTS>(lines, f); break;
-    default: x_launch<T, NH, X_SMALL, DOTS>(lines, f); break;
+    case X_WIDE: x_launch<T, NH, X_WIDE>(lines, f); break;
+    case X_MID: x_launch<T, NH, X_MID>(lines, f); break;
+    default: x_launch<T, NH, X_SMALL>(lines, f); break;
   }
 }
 
@@ -101,7 +101,7 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
                             double* dots_out, hipStream_t st) {
   if (bd.nv < 1 || bd.nv > kBasisDotsMax || io.rhs) return hipErrorInvalidValue;
   const long long lines = (long long)c.ny * c.nz;
-  const unsigned grid = x_blocks(int(sizeof(T)), NH, lines, x_shape(int(sizeof(T)), NH, lines), true);
+  const unsigned grid = x_blocks(int(sizeof(T)), NH, lines, x_shape(int(sizeof(T)), NH, lines));
   if (bd.defer_nb) *bd.defer_nb = 0;
   if (grid > (unsigned)kRedBlocksMax) {
     // more blocks than partial rows (the largest grids in float64): plain
@@ -119,7 +119,7 @@ hipError_t launch_xinv_dots(const Ctx& c, const NodalArgs& na, const PipeIO<T, T
   {
     const double node_b = xinv_node_bytes<T, TIn, TOut, EPI>(na, io) + 4.0 * 8 * bd.nv;
     ProfScope ps(c.prof, st, KK_XINV_DOTS, double(c.ng) * node_b + double(c.geom.cs) * lines * 2 * sizeof(T));
-    with_x_shape<T, NH, true>(lines, [&](auto shape, unsigned blocks, unsigned nt) {
+    with_x_shape<T, NH>(lines, [&](auto shape, unsigned blocks, unsigned nt) {
       hipLaunchKernelGGL((k_xinv<T, TIn, TOut, NH, EPI, true, decltype(shape)::value>), dim3(blocks), dim3(nt), 0,
                          st, io, reinterpret_cast<const cx<T>*>(c.spec), c.geom, na, tw, kd);
     });

@@ -1,0 +1,71 @@
+"""The preconditioned operators give the same bits with and without Arnoldi
+products: a caller may take the products or form them itself, and a solve is
+the same either way."""
+
+import numpy as np
+import pytest
+import torch
+
+import llg_workloads as W
+import paper_2607_15290_amd as P
+from oracle import operators
+from oracle.grid import Grid
+from tests.gpu_util import announce, assert_elem, both_params, dev, host, unit_field
+
+pytestmark = pytest.mark.gpu
+
+# x lengths of every FFT plan family of the x passes, on grids with more than
+# 256 wide blocks (in float64; 512 x 40 x 16 in float32 takes the mid shape)
+# and, last, one of the mid and one of the small shape
+SHAPES = [(32, 160, 128), (64, 96, 48), (96, 64, 80), (128, 64, 64), (160, 96, 80), (256, 64, 48), (512, 40, 16),
+          (80, 40, 32), (40, 10, 1)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_operator_bits_with_and_without_products(shape):
+    """M^{-1} A x in float64 and in float32, and the flexible form's A M^{-1} x,
+    without and with five products: equal bits; the values against the oracle
+    (1e-13; float32: one unit roundoff per butterfly level, four times that
+    over two nodal stages), the products against numpy's on the returned y
+    (1e-13 of the sum of absolute terms)."""
+    nx, ny, nz = shape
+    announce(f"products bits {shape}")
+    dt = W.dt_explicit_multiple(13.3, 0.02, max(nx, ny, nz), 2 if nz == 1 else 3)
+    prm, op = both_params(alpha=0.02, cexc=1.0, dt=dt, theta=0.5, shift=0.5, h_uniform=(0.0, 0.0, 1.0))
+    g = Grid(nx, ny, nz, h=1.0 / nx)
+    m = unit_field((nz, ny, nx), 71, smooth=40.0)
+    x = np.random.default_rng(72).standard_normal((4, nz, ny, nx))
+    ctx = P.Context(nx, ny, nz, 1.0 / nx, 0)
+    torch.manual_seed(73)
+    basis = torch.randn((5, 4, nz, ny, nx), dtype=torch.float64, device="cuda:0")
+    bh = host(basis).reshape(5, -1)
+    md, xd, mf = dev(m), dev(x), dev(m, torch.float32)
+    x32 = x.astype(np.float32).astype(np.float64)
+    tol = (sum(2 * int(np.ceil(np.log2(n))) for n in (nx, ny, nz) if n > 1) + 16) * 2.0 ** -24
+
+    def check_dots(yh, dots):
+        err = np.abs(host(dots)[:5] - bh @ yh.ravel()) / np.abs(bh * yh.ravel()).sum(axis=1)
+        assert err.max() <= 1e-13, err
+
+    y0 = host(P.llg_precond_op(ctx, prm, md, xd))
+    y, dots = P.llg_precond_op(ctx, prm, md, xd, basis=basis)
+    yh = host(y)
+    assert_elem(yh, operators.precond_op(g, op, m, x), 1e-13, "M^-1 A")
+    check_dots(yh, dots)
+    assert np.array_equal(yh, y0), "float64"
+
+    y0 = host(P.llg_precond_op_f32(ctx, prm, mf, xd, side=0)[0])
+    y, dots = P.llg_precond_op_f32(ctx, prm, mf, xd, side=0, basis=basis)
+    yh = host(y)
+    assert_elem(yh, operators.precond_op(g, op, host(mf), x32), 4 * tol, "float32 M^-1 A")
+    check_dots(yh, dots)
+    assert np.array_equal(yh, y0), "float32, left"
+
+    z0, z = (torch.empty((4, nz, ny, nx), dtype=torch.float32, device="cuda:0") for _ in range(2))
+    y0 = host(P.llg_precond_op_f32(ctx, prm, mf, xd, side=1, z=z0)[0])
+    y, dots = P.llg_precond_op_f32(ctx, prm, mf, xd, side=1, z=z, basis=basis)
+    yh = host(y)
+    assert_elem(yh, operators.matvec(g, op, host(mf), host(z)), tol, "float32 A z")
+    check_dots(yh, dots)
+    assert np.array_equal(host(z), host(z0)) and np.array_equal(yh, y0), "float32, flexible"
+    ctx.close()
