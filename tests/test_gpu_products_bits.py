@@ -20,6 +20,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(32, 160, 128), (64, 96, 48), (96, 64, 80), (128, 64, 64), (160, 96, 80), (256, 64, 48), (512, 40, 16),
           (80, 40, 32), (40, 10, 1)]
 
+# the mid shape with several lines per block and several threads per line; the
+# last block of the second holds four of its five lines, of the third one of
+# three; the last has the fewest blocks of the mid shape
+MID_SHAPES = [(80, 40, 32), (96, 48, 48), (160, 32, 32), (128, 24, 32)]
+
 
 @pytest.mark.parametrize("shape", SHAPES)
 def test_operator_bits_with_and_without_products(shape):
@@ -68,4 +73,31 @@ def test_operator_bits_with_and_without_products(shape):
     assert_elem(yh, operators.matvec(g, op, host(mf), host(z)), tol, "float32 A z")
     check_dots(yh, dots)
     assert np.array_equal(host(z), host(z0)) and np.array_equal(yh, y0), "float32, flexible"
+    ctx.close()
+
+
+@pytest.mark.parametrize("shape", MID_SHAPES)
+@pytest.mark.parametrize("nb", [1, 3, 4, 5, 17, 32])
+def test_products_in_the_mid_shape(shape, nb):
+    """M^{-1} A x against the oracle (1e-13) and its products with nb vectors
+    against numpy's (1e-13 of the sum of absolute terms), in float64 and in
+    the flexible float32 form."""
+    nx, ny, nz = shape
+    announce(f"mid shape {shape} nb={nb}")
+    dt = W.dt_explicit_multiple(13.3, 0.02, max(nx, ny, nz), 3)
+    prm, op = both_params(alpha=0.02, cexc=1.0, dt=dt, theta=0.5, shift=0.5, h_uniform=(0.0, 0.0, 1.0))
+    g = Grid(nx, ny, nz, h=1.0 / nx)
+    m = unit_field((nz, ny, nx), 75, smooth=40.0)
+    x = np.random.default_rng(76).standard_normal((4, nz, ny, nx))
+    ctx = P.Context(nx, ny, nz, 1.0 / nx, 0)
+    torch.manual_seed(77)
+    basis = torch.randn((nb, 4, nz, ny, nx), dtype=torch.float64, device="cuda:0")
+    bh = host(basis).reshape(nb, -1)
+    y, dots = P.llg_precond_op(ctx, prm, dev(m), dev(x), basis=basis)
+    y32, dots32 = P.llg_precond_op_f32(ctx, prm, dev(m, torch.float32), dev(x), side=1, basis=basis)
+    assert_elem(host(y), operators.precond_op(g, op, m, x), 1e-13, "M^-1 A")
+    for v, d in ((y, dots), (y32, dots32)):
+        vh = host(v).ravel()
+        err = np.abs(host(d)[:nb] - bh @ vh) / np.abs(bh * vh).sum(axis=1)
+        assert err.max() <= 1e-13, err
     ctx.close()

@@ -52,3 +52,29 @@ def test_largest_grid_has_more_blocks_than_partial_rows(geometry):
     assert (shape, lx) == ("wide", 2) and blocks == 73728 > rows
     shape, blocks, lx, rows = geometry(4, (512, 384, 384))
     assert (shape, lx) == ("wide", 4) and blocks == 36864 <= rows
+
+
+# grids of tests/test_gpu_products_bits.py: the shape that each is there for
+GRIDS = {
+    (8, "wide"): [(32, 160, 128), (64, 96, 48), (96, 64, 80), (128, 64, 64), (160, 96, 80), (256, 64, 48),
+                  (512, 40, 16)],
+    (4, "wide"): [(32, 160, 128), (64, 96, 48), (96, 64, 80), (128, 64, 64), (160, 96, 80), (256, 64, 48)],
+    (8, "mid"): [(80, 40, 32), (96, 48, 48), (160, 32, 32), (128, 24, 32)],
+    (4, "mid"): [(80, 40, 32), (96, 48, 48), (160, 32, 32), (128, 24, 32), (512, 40, 16)],
+    (8, "small"): [(40, 10, 1)],
+    (4, "small"): [(40, 10, 1)],
+}
+
+
+@pytest.mark.parametrize("elem_bytes, shape", GRIDS)
+def test_grids_of_the_products_tests(geometry, elem_bytes, shape):
+    for grid in GRIDS[elem_bytes, shape]:
+        assert geometry(elem_bytes, grid)[0] == shape, grid
+
+
+def test_edge_of_the_mid_shape(geometry):
+    """Several lines per block; 192 blocks are the fewest."""
+    for grid, blocks, lx in [((80, 40, 32), 214, 6), ((96, 48, 48), 461, 5), ((160, 32, 32), 342, 3),
+                             ((128, 24, 32), 192, 4)]:
+        assert geometry(8, grid)[:3] == ("mid", blocks, lx), grid
+    assert geometry(8, (128, 24, 24))[0] == "small"
