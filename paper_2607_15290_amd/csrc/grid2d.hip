@@ -43,11 +43,14 @@ __device__ __forceinline__ void grid_y(int n, int nlines, const cx<T>* __restric
   }
 }
 
-// The epilogues that the kernel takes, with the prologue each is used with.
-// Not EPI_FUSED: with and without Arnoldi products it has to give the same bits.
-#define LLG_FOR_GRID_EPI(X)                                                                     \
-  X(EPI_STORE3, PRO_COPY3) X(EPI_APPLY, PRO_COPY3) X(EPI_APPLY_T, PRO_M2T) X(EPI_MATVEC, PRO_COPY3) \
-  X(EPI_MATVEC_T, PRO_COPY3) X(EPI_RHS, PRO_COPY3) X(EPI_JT, PRO_COPY3) X(EPI_APPLY_SYM, PRO_COPY3) \
+// The epilogues that the kernel takes, with the prologue each is used with: the
+// operators in both precisions, the right-hand side, the solvers' other
+// operators and the Laplacian in float64.  Not EPI_FUSED: with and without
+// Arnoldi products it has to give the same bits.
+#define LLG_FOR_GRID_EPI(X)                                                                   \
+  X(EPI_APPLY, PRO_COPY3) X(EPI_APPLY_T, PRO_M2T) X(EPI_MATVEC, PRO_COPY3) X(EPI_MATVEC_T, PRO_COPY3)
+#define LLG_FOR_GRID_EPI_F64(X)                                                               \
+  X(EPI_STORE3, PRO_COPY3) X(EPI_RHS, PRO_COPY3) X(EPI_JT, PRO_COPY3) X(EPI_APPLY_SYM, PRO_COPY3) \
   X(EPI_FUSED_SYM, PRO_SMINUS)
 
 template <typename T, int EPI>
@@ -75,6 +78,7 @@ __global__ __launch_bounds__(kGridThreads) void k_grid2d(PipeIO<T, T, T> io, int
                                                          NodalArgs na, const cx<T>* __restrict__ twx,
                                                          const cx<T>* __restrict__ twy) {
   extern __shared__ double grid_lds[];
+  constexpr bool kF64 = std::is_same<T, double>::value;
   cx<T>* lds = reinterpret_cast<cx<T>*>(grid_lds);
   const int tid = threadIdx.x, ny = g.ny, nh = g.nh, sx = grid_stride(nh), npair = nh * ny;
   // rows (f, y) of nh + 1 values: node pairs, then the half spectrum along x
@@ -89,8 +93,8 @@ __global__ __launch_bounds__(kGridThreads) void k_grid2d(PipeIO<T, T, T> io, int
       prologue_compute<T, T, PRO>(raw, na, u);
     };
     if (pro == PRO_COPY3) fill(std::integral_constant<int, PRO_COPY3>{});
-    else if (pro == PRO_SMINUS) fill(std::integral_constant<int, PRO_SMINUS>{});
-    else fill(std::integral_constant<int, PRO_M2T>{});
+    else if (pro == PRO_M2T) fill(std::integral_constant<int, PRO_M2T>{});
+    else if constexpr (kF64) fill(std::integral_constant<int, PRO_SMINUS>{});
     const int y = e / nh, xp = e - y * nh;
 #pragma unroll
     for (int f = 0; f < 3; ++f) at_x(f * ny + y, xp) = u[f];
@@ -142,12 +146,13 @@ __global__ __launch_bounds__(kGridThreads) void k_grid2d(PipeIO<T, T, T> io, int
   for (int e = tid; e < npair; e += kGridThreads) {
     const int y = e / nh, xp = e - y * nh;
     const cx<T> fz[3] = {at_x(y, xp), at_x(ny + y, xp), at_x(2 * ny + y, xp)};
-    switch (epi) {
 #define LLG_CASE(E, P) \
   case E: grid_epilogue<T, E>(io, na, 2 * e, fz); break;
-      LLG_FOR_GRID_EPI(LLG_CASE)
-#undef LLG_CASE
+    switch (epi) { LLG_FOR_GRID_EPI(LLG_CASE) }
+    if constexpr (kF64) {
+      switch (epi) { LLG_FOR_GRID_EPI_F64(LLG_CASE) }
     }
+#undef LLG_CASE
   }
 }
 
@@ -160,8 +165,10 @@ bool grid_length(int nh, int ny) {
   return x && (false LLG_FOR_GRID_Y(LLG_EQ));
 #undef LLG_EQ
 }
+template <typename T>
 bool grid_modes(int pro, int epi) {
 #define LLG_EQ(E, P) || (epi == E && pro == P)
+  if (std::is_same<T, double>::value && (false LLG_FOR_GRID_EPI_F64(LLG_EQ))) return true;
   return false LLG_FOR_GRID_EPI(LLG_EQ);
 #undef LLG_EQ
 }
@@ -177,7 +184,8 @@ bool grid_modes(int pro, int epi) {
 constexpr size_t kGridBytes = 10240;
 template <typename T>
 bool grid2d_ok(const Ctx& c, int pro, int epi) {
-  return c.dim == 2 && size_t(c.ng) * sizeof(T) <= kGridBytes && grid_length(c.geom.nh, c.ny) && grid_modes(pro, epi);
+  return c.dim == 2 && size_t(c.ng) * sizeof(T) <= kGridBytes && grid_length(c.geom.nh, c.ny) &&
+         grid_modes<T>(pro, epi);
 }
 
 template <typename T>
