@@ -52,7 +52,7 @@ __device__ __forceinline__ cx<T> mul_dir_i(cx<T> a) {
 
 // ---------------------------------------------------------------------------
 // Radix plans: P points per thread, TPL = N / P threads per line (always a
-// power of two), up to four stages whose radices all divide P.
+// power of two), up to three stages whose radices all divide P.
 //   N:   2   4   8  16  32    64    128    256     512      1024
 //   R:  [2] [4] [8][16][8,4] [8,8] [16,8] [16,16] [8,8,8] [16,16,4]
 // Lengths 3 * 2^k and 5 * 2^k (the grids N = 24, 48 of the paper's 3D
@@ -72,38 +72,38 @@ constexpr int kPlanFine = 1 << 16;
 __host__ __device__ constexpr int plan_n(int key) { return key & (kPlanFine - 1); }
 
 struct Plan {
-  int p, nst, r0, r1, r2, r3;
+  int p, nst, r0, r1, r2;
 };
 __host__ __device__ constexpr Plan plan_of(int n) {
   switch (n) {
-    case 128 | kPlanFine: return {8, 3, 8, 4, 4, 1};
-    case 256 | kPlanFine: return {8, 3, 8, 8, 4, 1};
-    case 2: return {2, 1, 2, 1, 1, 1};
-    case 3: return {3, 1, 3, 1, 1, 1};
-    case 4: return {4, 1, 4, 1, 1, 1};
-    case 5: return {5, 1, 5, 1, 1, 1};
-    case 6: return {6, 1, 6, 1, 1, 1};
-    case 8: return {8, 1, 8, 1, 1, 1};
-    case 10: return {10, 1, 10, 1, 1, 1};
-    case 12: return {12, 1, 12, 1, 1, 1};
-    case 16: return {16, 1, 16, 1, 1, 1};
-    case 20: return {20, 1, 20, 1, 1, 1};
-    case 24: return {24, 1, 24, 1, 1, 1};
-    case 32: return {8, 2, 8, 4, 1, 1};
-    case 40: return {20, 2, 10, 4, 1, 1};
-    case 48: return {12, 2, 12, 4, 1, 1};
-    case 64: return {8, 2, 8, 8, 1, 1};
-    case 80: return {20, 2, 20, 4, 1, 1};
-    case 96: return {24, 2, 12, 8, 1, 1};
-    case 128: return {16, 2, 16, 8, 1, 1};
-    case 160: return {20, 3, 10, 4, 4, 1};
-    case 192: return {24, 2, 24, 8, 1, 1};
-    case 256: return {16, 2, 16, 16, 1, 1};
-    case 320: return {20, 3, 20, 4, 4, 1};
-    case 384: return {24, 3, 12, 8, 4, 1};
-    case 512: return {8, 3, 8, 8, 8, 1};
-    case 1024: return {16, 3, 16, 16, 4, 1};
-    default: return {0, 0, 1, 1, 1, 1};
+    case 128 | kPlanFine: return {8, 3, 8, 4, 4};
+    case 256 | kPlanFine: return {8, 3, 8, 8, 4};
+    case 2: return {2, 1, 2, 1, 1};
+    case 3: return {3, 1, 3, 1, 1};
+    case 4: return {4, 1, 4, 1, 1};
+    case 5: return {5, 1, 5, 1, 1};
+    case 6: return {6, 1, 6, 1, 1};
+    case 8: return {8, 1, 8, 1, 1};
+    case 10: return {10, 1, 10, 1, 1};
+    case 12: return {12, 1, 12, 1, 1};
+    case 16: return {16, 1, 16, 1, 1};
+    case 20: return {20, 1, 20, 1, 1};
+    case 24: return {24, 1, 24, 1, 1};
+    case 32: return {8, 2, 8, 4, 1};
+    case 40: return {20, 2, 10, 4, 1};
+    case 48: return {12, 2, 12, 4, 1};
+    case 64: return {8, 2, 8, 8, 1};
+    case 80: return {20, 2, 20, 4, 1};
+    case 96: return {24, 2, 12, 8, 1};
+    case 128: return {16, 2, 16, 8, 1};
+    case 160: return {20, 3, 10, 4, 4};
+    case 192: return {24, 2, 24, 8, 1};
+    case 256: return {16, 2, 16, 16, 1};
+    case 320: return {20, 3, 20, 4, 4};
+    case 384: return {24, 3, 12, 8, 4};
+    case 512: return {8, 3, 8, 8, 8};
+    case 1024: return {16, 3, 16, 16, 4};
+    default: return {0, 0, 1, 1, 1};
   }
 }
 // true for the plan keys that have a plan
@@ -111,7 +111,7 @@ __host__ __device__ constexpr bool plan_ok(int n) { return plan_of(n).p > 0; }
 __host__ __device__ constexpr int plan_p(int n) { return plan_of(n).p; }
 __host__ __device__ constexpr int plan_stages(int n) { return plan_of(n).nst; }
 __host__ __device__ constexpr int plan_radix(int n, int s) {
-  return s == 0 ? plan_of(n).r0 : s == 1 ? plan_of(n).r1 : s == 2 ? plan_of(n).r2 : plan_of(n).r3;
+  return s == 0 ? plan_of(n).r0 : s == 1 ? plan_of(n).r1 : plan_of(n).r2;
 }
 // product of the radices of the stages before s
 __host__ __device__ constexpr int plan_ns(int n, int s) {
@@ -429,7 +429,6 @@ __device__ __forceinline__ void line_fft(cx<T>* v, int t, Lds lds, const cx<T>* 
   if (on) stage_compute<T, KEY, 0, DIR>(v, t, tw, tws);
   if constexpr (NST > 1) next_stage<T, KEY, 1, DIR>(v, t, lds, tw, tws, on);
   if constexpr (NST > 2) next_stage<T, KEY, 2, DIR>(v, t, lds, tw, tws, on);
-  if constexpr (NST > 3) next_stage<T, KEY, 3, DIR>(v, t, lds, tw, tws, on);
 }
 
 }  // namespace llg
