@@ -534,10 +534,10 @@ llg_status cycle_dcgs2(const Ctx& c, const ArnoldiOpT<TW>& op, bool op_dots, con
                       defer && more ? &ride : nullptr));
     }
     // one round trip: the pass-1 dots p and the pass-2 dots of u_{j+1}, which
-    // the latter's reduction posts to the host mirror (on small grids the
-    // update pass itself does).  On small grids the next step's operator (on
-    // u_{j+1}, which no host decision changes) is queued before the host
-    // waits; when the cycle then ends, that work is discarded.
+    // the latter's reduction posts to the host mirror (a kernel of its own, or
+    // riding in the next operator's x-forward pass).  On small grids the next
+    // step's operator (on u_{j+1}, which no host decision changes) is queued
+    // before the host waits; when the cycle then ends, that work is discarded.
     ahead = speculate && more;
     ready = fuse;
     if (ahead) launch_op(j + 1, ((j + 1) & 1) ? c.dots_b : c.dots, ready);

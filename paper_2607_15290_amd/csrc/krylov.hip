@@ -1,10 +1,11 @@
 // Streaming vector kernels of the Krylov solvers and the steppers.
 //
-// All reductions are two-stage and deterministic: a grid whose size depends
-// only on the vector length accumulates per-thread partial sums in a fixed
-// order, reduces them across the block by wavefront shuffles, and writes one
-// partial per block; a second kernel sums the partials of each value in a
-// fixed tree.  The grid never depends on timing, so every reduced value is
+// All reductions are two-stage and deterministic: a launch whose size depends
+// only on the grid's lengths accumulates per-thread partial sums in a fixed
+// order, reduces them across the wavefront by lane exchanges (wave.h) and
+// across the block through LDS, and writes one partial per block; a second
+// kernel (on small grids the next pass) sums the partials of each value in a
+// fixed tree.  The launch never depends on timing, so every reduced value is
 // bitwise reproducible from run to run.
 //
 // Arnoldi orthogonalization is classical Gram-Schmidt with one
@@ -339,7 +340,12 @@ __global__ __launch_bounds__(kDcgsThreads) void k_dcgs_update(const double2* __r
 // time: one 16-byte pair per thread, whose loads are issued first; while they
 // are in flight every block reduces the operator's unreduced pass-1 products
 // (dp, or reads the reduced p) and forms gamma itself.  No non-temporal hints:
-// the basis stays in the caches.
+// up to about 2^18 nodes the basis stays in the caches.  Above that a cycle's
+// basis outgrows the 256 MB Infinity Cache and only the launch saved and the
+// XCD affinity remain, which still pay: float64 solves with the streaming pass
+// in its place above 2^18 nodes 96 x 64 x 64 2450 -> 2648 us, 80^3 3179 ->
+// 3271, 96^3 4895 -> 4945, and 128 x 128 x 64, the largest grid that comes
+// here, 5368 -> 5312.
 //
 // XCD affinity.  An XCD's L2 keeps what it read or wrote across kernels: a
 // buffer of 32 MB re-read by the same XCDs arrives at 12.8 TB/s, by other

@@ -64,11 +64,18 @@ inline unsigned x_blocks(int elem_bytes, int nh, long long lines, int shape) {
 }
 // Shape of the x passes on a grid: wide above LLG_X_WIDE_BLOCKS wide blocks
 // (one per CU), otherwise the mid shape if it gives a block to nearly every
-// CU.  With the line at 1024 blocks 160 x 96 x 80 solves (640) took 11% longer:
-// there the passes are bound by bytes, and 80 of 256 threads hold a line.
-// Below 256 the wide shape leaves CUs idle: 48^3 solves (36 blocks) 6.5 -> 4.3
-// ms with the mid shape, 32^2 Euler steps (1 block) 23.5 -> 16.7 with the
-// small one, 512^2 (64 blocks) the same with both.
+// CU.  Solves (float64, left float32 form; blocks in brackets) on both sides:
+//  * wide line at 640: 160 x 96 x 80 (480 wide) 6044 -> 6695 us, 4476 -> 4349:
+//    bound by bytes, and 36 of the mid shape's 256 threads hold a part of a
+//    line; 96^3 (576) 4896 -> 4926, 3826 -> 3657; 128 x 64 x 48 (384) 2533 ->
+//    2354, 2149 -> 1900;
+//  * wide line at 128, which leaves CUs idle: 512^2 (256 wide in float64, 128
+//    in float32) 1634 -> 1834, 1298 -> 1324; 64^3 (256) 1878 -> 1987, 1545 ->
+//    1683; 80^3 (200) 3176 -> 3462, 2673 -> 2871;
+//  * mid line at 100: 256^2 (128 mid) 747 -> 822, 870 -> 907; 80 x 40 x 24
+//    (160) 1178 -> 1053, 1359 -> 1281;
+//  * mid line at 300: 48^3 (231) 1104 -> 1425, 1250 -> 1279; 80 x 40 x 32 (214)
+//    1127 -> 1441, 1298 -> 1373; 128 x 24 x 32 (192) 1037 -> 1084, 1042 -> 1052.
 #ifndef LLG_X_WIDE_BLOCKS
 #define LLG_X_WIDE_BLOCKS 256
 #endif
@@ -203,7 +210,13 @@ struct RideReduce {
   double* out = nullptr;
   Post post;
 };
-constexpr int kRideMaxBlocks = 1100;  // 512^2: 1024 (and the rounding up per XCD)
+// Most update blocks of a pass whose reduction rides: the one block that sums
+// them ends with the pass around it up to there.  With the line at 500 blocks
+// float64 solves at 384^2 (576) 1232 -> 1307 us, 512^2 (1024) 1597 -> 1657, 64^3
+// (1024) 1880 -> 1919; at 4400 64 x 64 x 80 (1280) 2397 -> 2315, 128 x 64 x 48
+// (1536) 2632 -> 2556, 80^3 (2016) 3179 -> 3206, 128 x 128 x 64 (4096) 5368 ->
+// 5464.
+constexpr int kRideMaxBlocks = 1100;
 
 // Arnoldi inner products taken by an x-inverse pass on its own output (the
 // precision form's matvec): with basis directions u_0 at u0 and u_i at
@@ -228,7 +241,10 @@ struct BasisDots {
 };
 // Products are left for deferred reduction when the partials per value times
 // the blocks of the update pass, each of which sums them all, are at most this
-// (512^2: 512 x 1024).
+// (512^2: 512 x 1024).  With the line at 2^18 float64 solves at 512^2 1597 ->
+// 1566 us and 64^3 (2^19) 1880 -> 1827, the precision forms within 1%; at 2^21
+// 96 x 64 x 48 (2^19.4) 1899 -> 1992, 80 x 64 x 64 (2^19.8) 2071 -> 2222, 96 x
+// 64 x 64 (2^20.3) 2450 -> 2675, the precision forms 0.3-2.6% slower.
 constexpr long long kDeferMaxSums = 1 << 19;
 
 // Delayed-CGS2 pass 2 of Arnoldi step j carried by the first x pass of the
