@@ -48,8 +48,9 @@ struct DeferredDots {
 //   unew = (w - U gamma) / beta_j,   out = [U_i.unew (i <= j), unew.unew].
 // unew must not alias w or a basis column 0..j.  out and p (slots of c.dots)
 // are posted to the host.
-// With ride (filled when the pass has at most kRideMaxBlocks blocks) the
-// reduction into out is left to the next operator's x-forward pass.
+// With ride (filled when the pass has at most kRideMaxBlocks blocks and the
+// next operator's x-forward pass can carry it, x_rides) the reduction into out
+// is left to that pass.
 // With dp (dp->nb > 0) p is not read: the pass-1 products come from dp.
 hipError_t dcgs_update(const Ctx& c, const double* u0, const double* U1, long long ld, const DcgsCoef& cf,
                        const double* p, const double* w, double* unew, long long n, double* out, hipStream_t st,

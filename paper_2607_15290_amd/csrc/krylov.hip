@@ -706,7 +706,8 @@ static hipError_t dcgs_update_t(const Ctx& c, const double* u0, const double* U1
     JDispatch<UpdF>::run(cf.j, c, u0, U1, ld, gamma, cf, p, dp, w, unew, n, unsigned(nb), npair, st);
   }
   const Post post = next_post(c, out, p, cf.j + 1);
-  if (ride && nb <= kRideMaxBlocks) {
+  const int shape = x_shape(sizeof(TW), c.geom.nh, (long long)c.ny * c.nz);  // of the next operator's passes
+  if (ride && nb <= kRideMaxBlocks && x_rides(c.geom.nh, shape)) {
     ride->part = c.partial;
     ride->nb = nb;
     ride->nv = cf.j + 2;

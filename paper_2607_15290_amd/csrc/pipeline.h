@@ -87,6 +87,13 @@ inline int x_shape(int elem_bytes, int nh, long long lines) {
   return x_blocks(elem_bytes, nh, lines, X_MID) >= LLG_X_MID_BLOCKS ? X_MID : X_SMALL;
 }
 
+// Whether the x-forward pass of a shape can carry a riding reduction
+// (RideReduce).  The branch costs the wide passes of large grids, which never
+// take it, 1.1 us of 403 in the float32 M^{-1} x at 256^3, so it is left out
+// there: a wide pass of few enough nodes (kRideMaxBlocks) has lines of at
+// most 16 nodes.
+__host__ __device__ constexpr bool x_rides(int nh, int shape) { return shape != X_WIDE || nh <= 8; }
+
 // FFT plan key of the y / z passes: with LLG_AXIS_FINE_F64 the float64
 // passes at N = 256 take the finer plan as well.
 #ifndef LLG_AXIS_FINE_F64

@@ -472,13 +472,15 @@ __global__ __launch_bounds__((XCfg<T, NH, SHAPE>::NT)) void k_xfwd(const TIn* __
   constexpr bool NT = x_nt(SHAPE);
   __shared__ cx<T> lds[3 * C::LX * C::SL];
   const int tid = threadIdx.x;
-  if (ride.nv > 0 && blockIdx.x == gridDim.x - 1) {
-    rows_sum<C::NT / 64>(ride.part, ride.nb, ride.nv, [&](int q, double s) {
-      ride.out[q] = s;
-      if (ride.post.flag) ride.post.mirror[q] = s;
-    });
-    post_block(ride.post);
-    return;
+  if constexpr (x_rides(NH, SHAPE)) {
+    if (ride.nv > 0 && blockIdx.x == gridDim.x - 1) {
+      rows_sum<C::NT / 64>(ride.part, ride.nb, ride.nv, [&](int q, double s) {
+        ride.out[q] = s;
+        if (ride.post.flag) ride.post.mirror[q] = s;
+      });
+      post_block(ride.post);
+      return;
+    }
   }
   const long long nlines = (long long)g.ny * g.nz;
   const long long line0 = (long long)blockIdx.x * C::LX;
