@@ -88,7 +88,7 @@ def parse():
 
 
 def host_cores():
-    """Cores this process may run on (the GPU machine grants one GPU's share)."""
+    """Cores this process may run on."""
     try:
         n = len(os.sched_getaffinity(0))
     except AttributeError:
