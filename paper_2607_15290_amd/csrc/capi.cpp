@@ -245,7 +245,10 @@ ResidOp resid_op(const Ctx& c, int epi, const SymArgs& sym, const NodalArgs& na,
 }
 
 // The n values that the stream's latest reduction posted from the slots at dev.
-llg_status fetch(const Ctx& c, const double* dev, int n, hipStream_t st, double* host_out) {
+// A call that ends with them drains the stream (drain) instead of polling for
+// them first: one wait, not two.
+llg_status fetch(const Ctx& c, const double* dev, int n, hipStream_t st, double* host_out, bool drain = false) {
+  if (drain) CHK(hipStreamSynchronize(st));
   CHK(await_post(c, st));
   std::memcpy(host_out, c.hmirror + (dev - c.dots), sizeof(double) * n);
   return LLG_OK;
@@ -1042,7 +1045,8 @@ double ms_since(Clock::time_point t0) {
 // F = -(h_exc + h_dem + h_ani)(m); without it 1/2 cexc m.(-Delta_N m) - m.h_ext.
 // One pipeline (the field pipeline with a lower-order field) whose last pass
 // reduces the density: no field is stored.
-llg_status energy_of(const Ctx& c, const llg_params* p, const double* m, double* e, hipStream_t st) {
+llg_status energy_of(const Ctx& c, const llg_params* p, const double* m, double* e, hipStream_t st,
+                     bool drain = false) {
   const bool low = has_low(p);
   NodalArgs na = nodal_for(p);
   na.chat = low ? 1.0 : p->cexc;
@@ -1053,7 +1057,7 @@ llg_status energy_of(const Ctx& c, const llg_params* p, const double* m, double*
                                                  st)));
   CHK(reduce_flat(c, xinv_blocks(c), c.scal, st));
   double s;
-  CHK_STATUS(fetch(c, c.scal, 1, st, &s));
+  CHK_STATUS(fetch(c, c.scal, 1, st, &s, drain));
   const double vol = c.Lx * c.Ly * (c.dim == 3 ? c.Lz : 1.0);
   *e = s * vol / double(c.ng) + (low ? p->aniso_k * vol : 0.0);
   return LLG_OK;
@@ -1391,9 +1395,7 @@ llg_status llg_energy(llg_ctx* ctx, const llg_params* prm, const double* m, doub
   CHK_STATUS(check_params(prm));
   CHK_STATUS(ensure_device(ctx->c));
   CHK_STATUS(check_aligned({m}));
-  CHK_STATUS(energy_of(ctx->c, prm, m, energy, as_stream(stream)));
-  CHK(hipStreamSynchronize(as_stream(stream)));
-  return LLG_OK;
+  return energy_of(ctx->c, prm, m, energy, as_stream(stream), true);
 }
 
 llg_status llg_step_euler(llg_ctx* ctx, const llg_params* prm, double* m, double* v_out, double* lam_out,
