@@ -163,6 +163,22 @@ llg_status ensure_device(const Ctx& c) {
     if (s_ != LLG_OK) return s_;     \
   } while (0)
 
+// Drains the stream when a call that waits for the device returns before its
+// own last wait: a failing solve may have an operator queued (cycle_dcgs2) that
+// still reads and writes the caller's buffers.
+struct DrainOnError {
+  hipStream_t st;
+  bool armed = true;
+  ~DrainOnError() {
+    if (armed) (void)hipStreamSynchronize(st);
+  }
+  llg_status done() {
+    CHK(hipStreamSynchronize(st));
+    armed = false;
+    return LLG_OK;
+  }
+};
+
 // ---- pipelines (float64) ---------------------------------------------------
 hipError_t pipe_d(const Ctx& c, int pro, int epi, const SymArgs& sym, const NodalArgs& na, const double* in,
                   const double* m, double* out, hipStream_t st, const double* aux_v = nullptr,
@@ -1410,6 +1426,7 @@ llg_status llg_step_euler(llg_ctx* ctx, const llg_params* prm, double* m, double
   if (work_bytes < w.bytes) return fail(LLG_ENOMEM, "workspace smaller than llg_workspace_bytes()");
   CHK_STATUS(ensure_device(c));
   hipStream_t st = as_stream(stream);
+  DrainOnError drain{st};
   llg_params p1 = *prm;
   p1.theta = 1.0;
   llg_solver_opts o = *opts;
@@ -1446,7 +1463,7 @@ llg_status llg_step_euler(llg_ctx* ctx, const llg_params* prm, double* m, double
     const double a = p1.alpha;
     stats->dissipation_defect = e1 - e0 + a * p1.dt / (1 + a * a) * stats->v_norm2;
   }
-  CHK(hipStreamSynchronize(st));
+  CHK_STATUS(drain.done());
   return LLG_OK;
 }
 
@@ -1464,6 +1481,7 @@ llg_status llg_step_midpoint(llg_ctx* ctx, const llg_params* prm, double* m, dou
   if (work_bytes < w.bytes) return fail(LLG_ENOMEM, "workspace smaller than llg_workspace_bytes()");
   CHK_STATUS(ensure_device(c));
   hipStream_t st = as_stream(stream);
+  DrainOnError drain{st};
   const long long ng = c.ng;
   llg_params p2 = *prm;
   p2.theta = 0.5;
@@ -1577,7 +1595,7 @@ llg_status llg_step_midpoint(llg_ctx* ctx, const llg_params* prm, double* m, dou
     stats->inexact_correction = k / (1 + a * a) * (wq * d[3] - wq * d[4]);
     stats->max_len_err = len;
   }
-  CHK(hipStreamSynchronize(st));
+  CHK_STATUS(drain.done());
   if (!lconv) return fail(LLG_ENOCONV, "a Picard linear solve did not converge");
   if (!pconv) return fail(LLG_EPICARD, "Picard iteration reached picard_max");
   return LLG_OK;
@@ -1598,6 +1616,7 @@ llg_status llg_step_midpoint_adjoint(llg_ctx* ctx, const llg_params* prm, const 
   if (work_bytes < w.bytes) return fail(LLG_ENOMEM, "workspace smaller than llg_workspace_bytes()");
   CHK_STATUS(ensure_device(c));
   hipStream_t st = as_stream(stream);
+  DrainOnError drain{st};
   const long long ng = c.ng, n4 = 4 * ng;
   llg_params p2 = *prm;
   p2.theta = 0.5;
@@ -1672,7 +1691,7 @@ llg_status llg_step_midpoint_adjoint(llg_ctx* ctx, const llg_params* prm, const 
   CHK(adjoint_finish(c, nf, v, lam, w.x, w.l0, gbar, hbar_field, c.scal, st));
   double hs3[3];
   CHK_STATUS(fetch(c, c.scal, 3, st, hs3));
-  CHK(hipStreamSynchronize(st));
+  CHK_STATUS(drain.done());
   if (hbar_uniform)
     for (int i = 0; i < 3; ++i) hbar_uniform[i] += hs3[i];
   (void)n4;
